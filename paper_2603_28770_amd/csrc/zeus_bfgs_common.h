@@ -38,9 +38,10 @@ struct StartCounts {
 constexpr int kTabTrials = 32;
 
 __device__ __forceinline__ double step_length(const double *al, double shrink, int t) {
-  if (t < kTabTrials) return al[t];
-  double alpha = al[kTabTrials - 1];
-  for (int e = kTabTrials - 1; e < t; ++e) alpha = alpha * shrink;
+  // the load does not wait for the test, which hardly ever holds
+  double alpha = al[t < kTabTrials ? t : kTabTrials - 1];
+  if (t >= kTabTrials)
+    for (int e = kTabTrials - 1; e < t; ++e) alpha = alpha * shrink;
   return alpha;
 }
 
@@ -167,8 +168,8 @@ __device__ __forceinline__ void load_hot(ReqHot &w, const ReqDev &rq, int ri, in
 // Status of a start at iteration k that is neither non-finite nor converged:
 // the budget, else (first early-stop pass) the stopping bound read at the top
 // of the iteration, else still running (-1).
-__device__ __forceinline__ int budget_status(const ReqHot &q, int k, int bound) {
-  if (k == q.iter_bfgs) return q.stop_status;  // MAXITER, or STOPPED in the rerun
+__device__ __forceinline__ int budget_status(const ReqHot &q, int iter_bfgs, int k, int bound) {
+  if (k == iter_bfgs) return q.stop_status;  // MAXITER, or STOPPED in the rerun
   if (k >= bound) return ZEUS_ST_STOPPED;
   return -1;
 }
@@ -179,101 +180,246 @@ __device__ __forceinline__ int es_bound(const ReqHot &q) {
   return q.es ? es_load(q.es + kEsBound) : 0x7fffffff;
 }
 
-// Line-search trials per round: R trials of G / R lanes each.  64-lane
-// groups take two (d = 50 BFGS 3-7% faster than with four, d = 200 L-BFGS
-// 23%; one was slower): at 1.4 to 2.8 trials per iteration wider rounds
-// mostly evaluate trials past the accepted one.  Smaller groups take four:
-// two made Rastrigin at d <= 3 (many trials per iteration) up to 1.5 times
-// slower at every lane count from 4 to 32, and was even at d = 10.
+// The request's scalars that every iteration of a start needs, in registers: in
+// the LDS copy (ReqHot) each is a wait of its own on the iteration's path.
+// Where a group is a whole wave they are taken from one lane, so that they
+// sit in scalar registers.
 template <int G>
-constexpr int kRound = G == 64 ? 2 : (G < 4 ? G : 4);
+struct HotRegs {
+  int d, iter_bfgs, iter_ls, trace_len;
+  double tol, armijo_c;
+  bool es;  // the start may stop at its request's bound
+  __device__ __forceinline__ static int uni(int v) {
+    return G == 64 ? __builtin_amdgcn_readfirstlane(v) : v;
+  }
+  __device__ __forceinline__ static double uni(double v) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(
+        double, ((uint64_t)(uint32_t)uni((int)(b >> 32)) << 32) | (uint32_t)uni((int)(uint32_t)b));
+  }
+  // after the group's wave_sync that publishes q
+  __device__ __forceinline__ void take(const ReqHot &q) {
+    d = uni(q.d);
+    iter_bfgs = uni(q.iter_bfgs);
+    iter_ls = uni(q.iter_ls);
+    trace_len = uni(q.trace_len);
+    tol = uni(q.tol);
+    armijo_c = uni(q.armijo_c);
+    es = uni(q.es != nullptr ? 1 : 0) != 0;
+  }
+};
 
-// One Armijo search (Alg. 6) with the objective evaluated in number type U,
-// by a group of G lanes covering SLOTS term slots (SLOTS a multiple of G; the
-// point is xs + alpha ps, both in LDS and zero past the dimension).  A round
-// evaluates R consecutive trials of the sequence at once, each spread over
-// TP = G / R lanes holding B = SLOTS / TP consecutive term slots (zero past
-// the last term): a lane adds its slots pairwise and the trial's lanes finish
-// the pairwise sum with a butterfly.  The first trial that passes is the step
-// Alg. 6 returns.  Returns its index, or -1 when none of the iter_ls trials
-// passes.  When acc (the group's LDS) is given and a trial passes, the
-// trial's first lane writes its k-th term sum to acc[k] (objectives with a
-// term structure); the group sees it after its next wave_sync.
-template <int OBJ, int G, int SLOTS, class U>
-__device__ __forceinline__ int armijo_search(const GroupLanes<G> &L, const double *xs,
-                                             const double *ps, const double *al, const ReqHot &q,
-                                             double f, double ddir, double *acc = nullptr) {
+// Lanes per line-search trial.  A lane then holds SLOTS / TP consecutive term
+// slots, and a round gives a group of G lanes R = G / TP trials.  64-lane
+// groups take R = 2 (one trial a round was slower, four evaluate trials past
+// the accepted one: d = 50 BFGS 3-7% slower), smaller groups R = 4 (R = 2:
+// Ackley d = 2, 4,096 starts 12.9 ms against 7.6; Rosenbrock and Rastrigin
+// d = 10 within 2%); objectives in whole form take a trial per lane.  The
+// L-BFGS kernels choose their own (zeus_lbfgs_kernels.h).
+template <int OBJ, int G>
+constexpr int kTrialLanes = whole_form<Elem<OBJ>>::value ? 1 : G == 64 ? 32 : G < 4 ? 1 : G / 4;
+
+// What a search reads from its group's LDS slice: offsets in doubles.
+struct SearchLayout {
+  int stride;     // between the slices of a wave's groups
+  int xs, ps;     // the point and the direction, zero past the dimension
+  int al, q;      // step lengths, request
+  int fd;         // room for f and g'p at the point
+  int pick;       // one double of scratch
+  int acc;        // the accepted trial's term sums (-1: not kept)
+};
+
+// One trial's value, formed by TP lanes (this lane is number c of them) over
+// SLOTS term slots, at xs + alpha ps: a lane adds its B = SLOTS / TP consecutive
+// slots pairwise (zero past the last term) and the trial's lanes finish the
+// pairwise sum with a butterfly, so the value does not depend on which lanes
+// form it.  sums receives the term sums.
+template <int OBJ, int SLOTS, int TP, class U>
+__device__ __forceinline__ double trial_value(const double *xs, const double *ps, double alpha, int d,
+                                              int m, int c, U (&sums)[Elem<OBJ>::K]) {
   using E = Elem<OBJ>;
-  constexpr int R = kRound<G>, TP = G / R, B = SLOTS / TP;
-  constexpr uint64_t leaders = [] {  // bit r * TP for every trial r of a round
-    uint64_t b = 0;
-    for (int r = 0; r < R; ++r) b |= 1ull << (r * TP);
-    return b;
-  }();
-  if constexpr (whole_form<E>::value) {
-    // one trial per lane: trials base .. base + G - 1 in a round
-    for (int base = 0; base < q.iter_ls; base += G) {
-      const int t = base + L.j;
-      const double alpha = step_length(al, q.shrink, t);
-      const double ft = E::template trial<U>(xs, ps, alpha, q.d);
-      const bool ok = t < q.iter_ls && ft <= f + (q.armijo_c * alpha) * ddir;
-      const uint64_t hit = L.ballot(ok);
-      if (hit != 0ull) return base + (__ffsll((unsigned long long)hit) - 1);
-    }
-    return -1;
-  } else {
-  const int trial_slot = L.j / TP, c = L.j % TP;
-  const int d = q.d, m = q.m;
-  for (int base = 0; base < q.iter_ls; base += R) {
-    const int t = base + trial_slot;
-    const double alpha = step_length(al, q.shrink, t);
-    // Every slot is evaluated (indices clamped into the vectors) and the
-    // slots past the last term are replaced by zero afterwards: no branch
-    // per slot, so the loads of a chunk of CB slots are in flight together.
-    // A lane's B slots are taken CB at a time (a memory clobber between
-    // chunks keeps the next chunk's loads from being hoisted, which bounds
-    // the live registers); the pairwise tree over B is the tree over the
-    // chunk sums.
-    constexpr int CB = B < 4 ? B : 4;
-    U csum[E::K][B / CB];
+  constexpr int B = SLOTS / TP;
+  // Every slot is evaluated (indices clamped into the vectors) and the
+  // slots past the last term are replaced by zero afterwards: no branch
+  // per slot, so the loads of a chunk of CB slots are in flight together.
+  // A lane's B slots are taken CB at a time (a memory clobber between
+  // chunks keeps the next chunk's loads from being hoisted, which bounds
+  // the live registers); the pairwise tree over B is the tree over the
+  // chunk sums.
+  constexpr int CB = B < 4 ? B : 4;
+  U csum[E::K][B / CB];
 #pragma unroll
-    for (int cb = 0; cb < B / CB; ++cb) {
-      if (cb > 0) asm volatile("" ::: "memory");
-      U tv[E::K][CB];
+  for (int cb = 0; cb < B / CB; ++cb) {
+    if (cb > 0) asm volatile("" ::: "memory");
+    U tv[E::K][CB];
 #pragma unroll
-      for (int b = 0; b < CB; ++b) {
-        const int i = c * B + cb * CB + b;
-        U w[E::W], out[E::K];
+    for (int b = 0; b < CB; ++b) {
+      const int i = c * B + cb * CB + b;
+      U w[E::W], out[E::K];
 #pragma unroll
-        for (int e = 0; e < E::W; ++e) {
-          const int ie = i + e < SLOTS ? i + e : SLOTS - 1;
-          w[e] = (U)(xs[ie] + alpha * ps[ie]);
-        }
+      for (int e = 0; e < E::W; ++e) {
+        const int ie = i + e < SLOTS ? i + e : SLOTS - 1;
+        w[e] = (U)(xs[ie] + alpha * ps[ie]);
+      }
+      // With a trial per lane, slot b is term b on every lane: no lane of
+      // the wave may need it (d = 2 and 3 in groups of four lanes)
+      bool any = true;
+      if constexpr (TP == 1)
+        if (b > 0) any = __ballot(i < m) != 0ull;
+#pragma unroll
+      for (int kk = 0; kk < E::K; ++kk) tv[kk][b] = U(0);
+      if (any) {
         E::template term<U>(w, out);
 #pragma unroll
         for (int kk = 0; kk < E::K; ++kk) tv[kk][b] = i < m ? out[kk] : U(0);
       }
-#pragma unroll
-      for (int kk = 0; kk < E::K; ++kk) csum[kk][cb] = reg_tree_sum<CB, U>(tv[kk]);
     }
-    U sums[E::K];
 #pragma unroll
-    for (int kk = 0; kk < E::K; ++kk)
-      sums[kk] = lane_tree_sum<TP, U>(reg_tree_sum<B / CB, U>(csum[kk]));
-    const double ft = (double)E::template outer<U>(d, sums);
-    const bool ok = t < q.iter_ls && ft <= f + (q.armijo_c * alpha) * ddir;
-    const uint64_t hit = L.ballot(ok) & leaders;
-    if (hit != 0ull) {
-      const int r = (__ffsll((unsigned long long)hit) - 1) / TP;  // the passing trial's slot
-      static_assert(E::K <= kMaxSums, "more term sums than the slots kept for them");
-      if (acc && L.j == r * TP)
+    for (int kk = 0; kk < E::K; ++kk) csum[kk][cb] = reg_tree_sum<CB, U>(tv[kk]);
+  }
 #pragma unroll
-        for (int kk = 0; kk < E::K; ++kk) acc[kk] = (double)sums[kk];
-      return base + r;
+  for (int kk = 0; kk < E::K; ++kk)
+    sums[kk] = lane_tree_sum<TP, U>(reg_tree_sum<B / CB, U>(csum[kk]));
+  return (double)E::template outer<U>(d, sums);
+}
+
+// The Armijo searches (Alg. 6) of a wave's groups, the objective evaluated in
+// number type U.  Every lane of the wave must call it; need (the same on all
+// lanes of a group) says which groups search, the others lend their lanes;
+// hot, f and ddir are the scalars, the value and g'p of the lane's own group.
+// Returns, on the lanes of a searching group, the index of the first trial
+// that passes, or -1 when none of the iter_ls trials does: the step the
+// sequential loop of Alg. 6 returns.
+//
+// A round evaluates 64 / TP trials, TP lanes each.  While more than half of
+// the wave's groups search, each tries R = G / TP trials a round on its own
+// lanes.  After that the lanes are shared out among the groups that have not
+// found their step (as many equal shares as the next power of two), so the
+// fewer they are the more trials each tries at once.  A start that stalls,
+// every trial of every search failing, sets the end of a launch by itself;
+// with its own lanes alone it took 5 rounds an iteration beside idle ones.
+// Bound by latency there.  BFGS phase with fixed lanes and with shared ones:
+// Ackley d = 10, 16,384 starts 15.9 -> 7.4 ms, Rastrigin d = 6, 16,384 starts
+// 5.5 -> 3.4 ms, d = 2, 65,536 starts 9.2 -> 8.1 ms; where no start stalls the
+// test after each round costs 0-4% (Rosenbrock d = 2, 65,536 starts 1.25 -> 1.27 ms).
+// Sharing from the first failed round on, whatever the number of groups left,
+// was slower (Ackley d = 2, 4,096 starts 9.4 ms against 7.6), and so was
+// sharing after two rounds (Rastrigin d = 6 4.3 ms).
+//
+// The group sees what is written to acc after its next wave_sync.
+template <int OBJ, int G, int SLOTS, int TP, class U>
+__device__ __forceinline__ int wave_search(const GroupLanes<G> &L, const HotRegs<G> &hot, bool need,
+                                           double f, double ddir, double *wave_lds,
+                                           const SearchLayout &lay) {
+  using E = Elem<OBJ>;
+  constexpr int R = G / TP, S = 64 / G;
+  static_assert(TP >= 1 && TP <= G && G % TP == 0 && SLOTS % TP == 0, "whole trials per group");
+  static_assert(E::K <= kMaxSums, "more term sums than the slots kept for them");
+  const int lane = threadIdx.x & 63, c = lane % TP;
+  const double *own = wave_lds + L.grp * lay.stride;
+  const ReqHot &oq = *reinterpret_cast<const ReqHot *>(own + lay.q);
+  constexpr uint64_t leaders = [] {  // bit r * TP for every trial r of a group
+    uint64_t b = 0;
+    for (int r = 0; r < R; ++r) b |= 1ull << (r * TP);
+    return b;
+  }();
+  const int r = L.j / TP, iter_ls = hot.iter_ls;
+  int taken = -1;
+  bool open = need;  // the lane's own group still searches
+  int base = 0;
+  uint64_t todo;     // the groups that search, bit G * group
+  {
+    do {
+      const int t = base + r;
+      const double alpha = step_length(own + lay.al, oq.shrink, t);
+      // the trial's bound, formed before the terms rather than behind them
+      const double bound = f + (hot.armijo_c * alpha) * ddir;
+      double ft = 0.0;
+      U sums[E::K];
+      if constexpr (whole_form<E>::value) {
+        // a group that has not searched yet has no request in its slice
+        if (open) ft = E::template trial<U>(own + lay.xs, own + lay.ps, alpha, oq.d);
+      } else {
+        ft = trial_value<OBJ, SLOTS, TP, U>(own + lay.xs, own + lay.ps, alpha, oq.d, oq.m, c, sums);
+      }
+      const bool ok = open & (t < iter_ls) & (ft <= bound);
+      const uint64_t mine = L.ballot(ok) & leaders;
+      if (mine != 0ull) {
+        const int first = (__ffsll((unsigned long long)mine) - 1) / TP;  // the passing trial's place
+        taken = base + first;
+        open = false;
+        if constexpr (!whole_form<E>::value)
+          if (lay.acc >= 0 && L.j == first * TP)
+#pragma unroll
+            for (int kk = 0; kk < E::K; ++kk)
+              wave_lds[L.grp * lay.stride + lay.acc + kk] = (double)sums[kk];
+        if constexpr (S == 1) return taken;  // the wave's only group (mine is a scalar there)
+      }
+      base += R;
+      open = open && base < iter_ls;
+      todo = S == 1 ? 0ull : __ballot(open && L.j == 0);
+    } while (S == 1 ? base < iter_ls : __popcll(todo) > S / 2);
+  }
+  if constexpr (S > 1) {
+    constexpr uint64_t all_leaders = [] {  // bit s * TP for every trial s of a round
+      uint64_t b = 0;
+      for (int s = 0; s < 64 / TP; ++s) b |= 1ull << (s * TP);
+      return b;
+    }();
+    while (todo != 0ull) {
+      // share the lanes out: 64 >> (6 - share) of them per group, in group order
+      const int n = __popcll(todo);
+      int share = 6;  // log2 of a share's lanes
+      while ((64 >> share) < n) --share;
+      const int per = (1 << share) / TP;  // trials per share
+      const int rank = __popcll(todo & ((1ull << (L.grp * G)) - 1ull));
+      wave_sync();  // every lane has read the previous shares
+      if (open && L.j == 0) {
+        *reinterpret_cast<int *>(wave_lds + rank * lay.stride + lay.pick) = L.grp;
+        wave_lds[L.grp * lay.stride + lay.fd] = f;
+        wave_lds[L.grp * lay.stride + lay.fd + 1] = ddir;
+      }
+      wave_sync();
+      const int s = lane >> share;
+      const bool valid = s < n;
+      const int target = *reinterpret_cast<const int *>(wave_lds + (valid ? s : 0) * lay.stride + lay.pick);
+      double *sl = wave_lds + target * lay.stride;  // the slice of the group the lane works for
+      const ReqHot &q = *reinterpret_cast<const ReqHot *>(sl + lay.q);
+      const int t = base + ((lane / TP) & (per - 1));
+      const double alpha = step_length(sl + lay.al, q.shrink, t);
+      const int target_ls = q.iter_ls;
+      const double bound = sl[lay.fd] + (q.armijo_c * alpha) * sl[lay.fd + 1];
+      double ft = 0.0;
+      U sums[E::K];
+      if constexpr (whole_form<E>::value) {
+        if (valid) ft = E::template trial<U>(sl + lay.xs, sl + lay.ps, alpha, q.d);
+      } else {
+        ft = trial_value<OBJ, SLOTS, TP, U>(sl + lay.xs, sl + lay.ps, alpha, q.d, q.m, c, sums);
+      }
+      const bool ok = valid & (t < target_ls) & (ft <= bound);
+      const uint64_t hits = __ballot(ok) & all_leaders;
+      const uint64_t field = share == 6 ? ~0ull : (1ull << (1 << share)) - 1ull;  // a share's lanes
+      if constexpr (!whole_form<E>::value) {
+        // the first lane of a share's first passing trial keeps its sums
+        const uint64_t before = hits & ((1ull << lane) - 1ull);
+        if (lay.acc >= 0 && ((hits >> lane) & 1ull) && (before >> (s << share)) == 0ull)
+#pragma unroll
+          for (int kk = 0; kk < E::K; ++kk) sl[lay.acc + kk] = (double)sums[kk];
+      }
+      if (open) {
+        const uint64_t mine = (hits >> ((rank << share) & 63)) & field;
+        if (mine != 0ull) {
+          taken = base + (__ffsll((unsigned long long)mine) - 1) / TP;
+          open = false;
+        } else {
+          open = base + per < iter_ls;
+        }
+      }
+      base += per;
+      todo = __ballot(open && L.j == 0);
     }
   }
-  return -1;
-  }
+  return taken;
 }
 
 }  // namespace zeus

@@ -304,7 +304,7 @@ void bfgs_hybrid_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t tot
     else if (norm_below(gg, q.tol))
       status = ZEUS_ST_CONVERGED;
     else
-      status = budget_status(q, k, bound);
+      status = budget_status(q, q.iter_bfgs, k, bound);
     if (status >= 0) {
       const ReqDev &rq = reqs[q.ri];
       const int tl = q.trace_len;

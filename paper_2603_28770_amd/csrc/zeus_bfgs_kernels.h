@@ -42,9 +42,13 @@ struct GroupShm {
   ReqHot *q;   // the start's request
 };
 
-// Doubles per group slice.
+// Doubles per group slice (the last one is the searches' scratch).
 __device__ __host__ __forceinline__ constexpr int group_stride(int G) {
-  return 2 * G + 3 * tile_vec_len(G) + kTabTrials + kHotDoubles;
+  return 2 * G + 3 * tile_vec_len(G) + kTabTrials + kHotDoubles + 3;
+}
+__device__ __host__ __forceinline__ constexpr SearchLayout group_search_layout(int G) {
+  const int al = 2 * G + 3 * tile_vec_len(G), q = al + kTabTrials, fd = q + kHotDoubles;
+  return SearchLayout{group_stride(G), 0, G, al, q, fd, fd + 2, -1};
 }
 
 // T = double: every step in FP64.
@@ -64,10 +68,16 @@ __device__ __host__ __forceinline__ constexpr int group_stride(int G) {
 // compiler keeps the 64-lane kernels of the transcendental objectives at one
 // wave (256 VGPRs plus AGPRs); asking for two costs a few dozen spilled
 // registers but hides far more latency (Ackley d = 50: 1.5x faster), and
-// three waves help Rastrigin's 16-lane kernel the same way.  Other kernels
-// reach their occupancy without the request.
+// three waves help Rastrigin's 16-lane kernel the same way.  The polynomial
+// objectives' kernels lie a few registers above the next occupancy at 8 to 32
+// lanes (Rosenbrock d = 20 in mixed precision, 16,384 starts: 1.88 ms at two
+// waves, 1.57 at three; d = 10, 65,536 starts: 1.21 at three, 1.14 at four).  Other kernels reach their occupancy without the request, and
+// user code is of unknown size.
 template <int OBJ, int G>
-constexpr int kBfgsWaves = G == 64 ? 2 : (G == 16 && OBJ == kRastrigin) ? 3 : 1;
+constexpr int kBfgsWaves = G == 64 ? 2
+                           : OBJ == kUser || OBJ == kAckley ? 1
+                           : OBJ == kRastrigin ? (G == 16 ? 3 : 1)
+                           : G == 32 ? 3 : G == 8 || G == 16 ? 4 : 1;
 
 template <int OBJ, int G, class T>
 __global__ __launch_bounds__(kBfgsBlock) __attribute__((amdgpu_waves_per_eu(kBfgsWaves<OBJ, G>)))
@@ -91,6 +101,9 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
     sh.al = sh.us + VL;
     sh.q = reinterpret_cast<ReqHot *>(sh.al + kTabTrials);
   }
+  double *wave_lds = smem + (size_t)((threadIdx.x >> 6) * S) * group_stride(G);
+  constexpr SearchLayout lay = group_search_layout(G);
+  constexpr int TP = kTrialLanes<OBJ, G>;
 
   bool own = false;
   Tile<G> H;  // this lane's tile of the inverse Hessian (identity in the padding)
@@ -98,15 +111,18 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
   int64_t idx = -1;
   int k = 0, ls_trials = 0;
   StartCounts cnt{0, 0};  // the start's update skips and direction resets
-  bool fresh = false, first = true;
+  bool fresh = false, first = true, alive = true;
   bool hi = !kMixed;  // evaluating in FP64 (always, unless mixed precision)
   const int es_pass = es_pass_of(hdr);
   int claims = 0;  // starts claimed after the first (second early-stop pass)
   int cur_ri = -1;  // the request whose scalars and step lengths the group's LDS holds
+  HotRegs<G> hot{};
 
   for (;;) {
     // -- claim a start when idle ------------------------------------------
-    if (idx < 0) {
+    // A group without starts left stays in the loop until its whole wave is
+    // done: its lanes serve the searches of the wave's other groups.
+    while (alive && idx < 0) {
       // the first start of a group is its own index; later ones come from
       // the counter, after the starts taken that way
       const unsigned long long groups = (unsigned long long)gridDim.x * (kBfgsBlock / G);
@@ -122,7 +138,10 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
         if (j == 0) got = groups + atomicAdd((unsigned long long *)&hdr->queue, 1ull);
         got = __shfl(got, L.grp * G, 64);
       }
-      if (got >= (unsigned long long)total) break;
+      if (got >= (unsigned long long)total) {
+        alive = false;
+        break;
+      }
       const int ri = request_of(reqs, nreq, (int64_t)got);
       const ReqDev &rq = reqs[ri];
       idx = (int64_t)got - rq.start_offset + rq.slice_first;
@@ -135,6 +154,8 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
         if (j == 0) load_hot<OBJ>(*sh.q, rq, ri, es_pass);
         fill_step_lengths(sh.al, rq.shrink, j, G);
         cur_ri = ri;
+        wave_sync();
+        hot.take(*sh.q);
       }
       own = j < d0;
       xj = own ? rq.ws.x[idx * d0 + j] : 0.0;  // x <- swarm[i]
@@ -146,145 +167,166 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
       fresh = true;
       hi = !kMixed;
     }
+    if (S == 1 ? !alive : __ballot(alive) == 0ull) break;
     wave_sync();
     const ReqHot &q = *sh.q;
-    const int d = q.d;
-    // the group's stopping bound, read early (its use is at the termination
-    // test) and taken from one lane: the bound falls while the kernel runs
-    const int bound = __shfl(es_bound(q), L.grp * G, 64);
+    const int d = hot.d;
+    bool search = false;  // the group's start goes on to a line search
+    double ddir = 0.0;
+    if (S == 1 || alive) do {
+      // the group's stopping bound, read early (its use is at the termination
+      // test) and taken from one lane: the bound falls while the kernel runs
+      int bound = 0x7fffffff;
+      if (hot.es) bound = __shfl(es_load(q.es + kEsBound), L.grp * G, 64);
 
-    // -- value and gradient at xs (dual numbers, one direction per lane) ----
-    double gn, fn;
-    if (hi)
-      fn = group_value_grad<OBJ, G, double>(L, d, sh.xs, &gn);
-    else
-      fn = group_value_grad<OBJ, G, T>(L, d, sh.xs, &gn);
+      // -- value and gradient at xs (dual numbers, one direction per lane) ----
+      double gn, fn;
+      if (hi)
+        fn = group_value_grad<OBJ, G, double>(L, d, sh.xs, &gn);
+      else
+        fn = group_value_grad<OBJ, G, T>(L, d, sh.xs, &gn);
 
-    // y's and g'g are formed together (independent butterflies overlap);
-    // right after a claim or an escalation y's is not used
-    const double yj = gn - gj;  // zero beyond the dimension
-    const double sy = lane_tree_sum<G, double>(yj * sj);
-    const double gg = lane_tree_sum<G, double>(gn * gn);
+      // y's and g'g are formed together (independent butterflies overlap);
+      // right after a claim or an escalation y's is not used
+      const double yj = gn - gj;  // zero beyond the dimension
+      const double sy = lane_tree_sum<G, double>(yj * sj);
+      const double gg = lane_tree_sum<G, double>(gn * gn);
 
-    // -- after a step: y and the rank-2 inverse-Hessian update --------------
-    if (!fresh) {
-      if (sy > 0.0) {  // curvature condition; skip the update otherwise
-        const double rho = 1.0 / sy;
-        // every lane: the tile sums cross lanes.  From 16 lanes on the tiles
-        // take the vector by row broadcasts from the lanes' own entries.
-        double uj;
-        if constexpr (kTileCols<G> == 16) {
-          uj = H.matvec_bcast(yj);
+      // -- after a step: y and the rank-2 inverse-Hessian update --------------
+      if (!fresh) {
+        if (sy > 0.0) {  // curvature condition; skip the update otherwise
+          const double rho = 1.0 / sy;
+          // every lane: the tile sums cross lanes.  From 16 lanes on the tiles
+          // take the vector by row broadcasts from the lanes' own entries.
+          double uj;
+          if constexpr (kTileCols<G> == 16) {
+            uj = H.matvec_bcast(yj);
+          } else {
+            sh.vs[vpos<G>(j)] = yj;
+            wave_sync();
+            uj = H.matvec(sh.vs, j);
+          }
+          uj = own ? uj : 0.0;
+          const double yu = lane_tree_sum<G, double>(yj * uj);
+          if constexpr (kTileRows<G> > 1 || kTileCols<G> < 16) {  // rows of other lanes
+            sh.us[vpos<G>(j)] = uj;
+            sh.ss[vpos<G>(j)] = sj;
+            wave_sync();
+          }
+          const double beta = (rho * rho) * yu + rho;
+          // H+ = H - rho (s u' + u s') + beta s s'   (u = H y); inf * 0 would
+          // have reached the padding when a coefficient is not finite
+          bool fin;
+          if constexpr (kTileCols<G> == 16)
+            fin = H.rank2_bcast(rho, beta, sh.us, sh.ss, uj, sj, j, sj, uj);
+          else
+            fin = H.rank2(rho, beta, sh.us, sh.ss, j, sj, uj);
+          if (!fin) H.restore_padding(j, d);
         } else {
-          sh.vs[vpos<G>(j)] = yj;
-          wave_sync();
-          uj = H.matvec(sh.vs, j);
+          ++cnt.skips;
         }
-        uj = own ? uj : 0.0;
-        const double yu = lane_tree_sum<G, double>(yj * uj);
-        if constexpr (kTileRows<G> > 1 || kTileCols<G> < 16) {  // rows of other lanes
-          sh.us[vpos<G>(j)] = uj;
-          sh.ss[vpos<G>(j)] = sj;
-          wave_sync();
-        }
-        const double beta = (rho * rho) * yu + rho;
-        // H+ = H - rho (s u' + u s') + beta s s'   (u = H y); inf * 0 would
-        // have reached the padding when a coefficient is not finite
-        bool fin;
-        if constexpr (kTileCols<G> == 16)
-          fin = H.rank2_bcast(rho, beta, sh.us, sh.ss, uj, sj, j, sj, uj);
-        else
-          fin = H.rank2(rho, beta, sh.us, sh.ss, j, sj, uj);
-        if (!fin) H.restore_padding(j, d);
-      } else {
-        ++cnt.skips;
+        ++k;
       }
-      ++k;
-    }
-    gj = gn;
-    f = fn;
-    fresh = false;
-    if (q.trace_len && own && k < q.trace_len) reqs[q.ri].trace[(idx * q.trace_len + k) * d + j] = xj;
+      gj = gn;
+      f = fn;
+      fresh = false;
+      if (own && k < hot.trace_len) reqs[q.ri].trace[(idx * hot.trace_len + k) * d + j] = xj;
 
-    // -- termination: non-finite, ||g|| < Theta, budget ---------------------
-    const bool bad = (own && !__builtin_isfinite(gj)) || !__builtin_isfinite(f);
-    const bool any_bad = L.ballot(bad) != 0ull;
-    if (kMixed && !hi && (any_bad || norm_below(gg, 10.0 * q.tol))) {
-      hi = true;  // escalate: re-evaluate this point in FP64
-      fresh = true;
-      continue;
-    }
-    int status = -1;
-    if (any_bad)
-      status = ZEUS_ST_NONFINITE;
-    else if (norm_below(gg, q.tol))
-      status = ZEUS_ST_CONVERGED;
-    else
-      status = budget_status(q, k, bound);
-    if (status >= 0) {
-      const ReqDev &rq = reqs[q.ri];
-      const int tl = q.trace_len;
-      if (status == ZEUS_ST_CONVERGED && q.es && j == 0) es_converged(q.es, k, q.iter_bfgs, q.es_c);
-      if (own) rq.out_x[idx * d + j] = xj;
-      if (kMixed && !hi) f = group_value<OBJ, G, double>(L, d, sh.xs);  // FP64 value at x
-      if (j == 0) {
-        rq.out_f[idx] = f;
-        rq.out_iters[idx] = k;
-        rq.out_status[idx] = status;
-        if (rq.out_ls) rq.out_ls[idx] = ls_trials;
-        if (rq.out_skips) rq.out_skips[idx] = cnt.skips;
-        if (rq.out_resets) rq.out_resets[idx] = cnt.resets;
-      }
-      if (tl && own)
-        for (int kk = k + 1; kk < tl; ++kk)
-          rq.trace[(idx * tl + kk) * d + j] = __builtin_nan("");
-      idx = -1;
-      continue;
-    }
-
-    // -- search direction p = -H g (reset to -g if not a descent direction) -
-    double hg;  // every lane: the tile sums cross lanes
-    if constexpr (kTileCols<G> == 16) {
-      hg = H.matvec_bcast(gj);
-    } else {
-      sh.vs[vpos<G>(j)] = gj;
-      wave_sync();
-      hg = H.matvec(sh.vs, j);
-    }
-    pj = own ? -hg : 0.0;
-    double ddir = lane_tree_sum<G, double>(gj * pj);
-    if (!(ddir < 0.0)) {
-      H.identity(j);
-      pj = own ? -gj : 0.0;
-      ddir = lane_tree_sum<G, double>(gj * pj);
-      ++cnt.resets;
-    }
-    sh.ps[j] = pj;
-    wave_sync();
-
-    // -- Armijo backtracking (Alg. 6) ---------------------------------------
-    int taken;
-    if (hi) {
-      taken = armijo_search<OBJ, G, G, double>(L, sh.xs, sh.ps, sh.al, *sh.q, f, ddir);
-    } else {
-      taken = armijo_search<OBJ, G, G, T>(L, sh.xs, sh.ps, sh.al, *sh.q, f, ddir);
-      if (taken < 0) {
-        ls_trials += q.iter_ls;
-        hi = true;  // escalate: FP32 cannot resolve this decrease
+      // -- termination: non-finite, ||g|| < Theta, budget ---------------------
+      const bool bad = (own && !__builtin_isfinite(gj)) || !__builtin_isfinite(f);
+      const bool any_bad = L.ballot(bad) != 0ull;
+      if (kMixed && !hi && (any_bad || norm_below(gg, 10.0 * hot.tol))) {
+        hi = true;  // escalate: re-evaluate this point in FP64
         fresh = true;
-        continue;
+        break;
       }
+      int status = -1;
+      if (any_bad)
+        status = ZEUS_ST_NONFINITE;
+      else if (norm_below(gg, hot.tol))
+        status = ZEUS_ST_CONVERGED;
+      else
+        status = budget_status(q, hot.iter_bfgs, k, bound);
+      if (status >= 0) {
+        const ReqDev &rq = reqs[q.ri];
+        const int tl = hot.trace_len;
+        if (status == ZEUS_ST_CONVERGED && hot.es && j == 0) es_converged(q.es, k, q.iter_bfgs, q.es_c);
+        if (own) rq.out_x[idx * d + j] = xj;
+        if (kMixed && !hi) f = group_value<OBJ, G, double>(L, d, sh.xs);  // FP64 value at x
+        if (j == 0) {
+          rq.out_f[idx] = f;
+          rq.out_iters[idx] = k;
+          rq.out_status[idx] = status;
+          if (rq.out_ls) rq.out_ls[idx] = ls_trials;
+          if (rq.out_skips) rq.out_skips[idx] = cnt.skips;
+          if (rq.out_resets) rq.out_resets[idx] = cnt.resets;
+        }
+        if (tl && own)
+          for (int kk = k + 1; kk < tl; ++kk)
+            rq.trace[(idx * tl + kk) * d + j] = __builtin_nan("");
+        idx = -1;
+        break;
+      }
+
+      // -- search direction p = -H g (reset to -g if not a descent direction) -
+      double hg;  // every lane: the tile sums cross lanes
+      if constexpr (kTileCols<G> == 16) {
+        hg = H.matvec_bcast(gj);
+      } else {
+        sh.vs[vpos<G>(j)] = gj;
+        wave_sync();
+        hg = H.matvec(sh.vs, j);
+      }
+      pj = own ? -hg : 0.0;
+      ddir = lane_tree_sum<G, double>(gj * pj);
+      if (!(ddir < 0.0)) {
+        H.identity(j);
+        pj = own ? -gj : 0.0;
+        ddir = lane_tree_sum<G, double>(gj * pj);
+        ++cnt.resets;
+      }
+      sh.ps[j] = pj;
+      wave_sync();
+      search = true;
+    } while (false);
+
+    // -- Armijo backtracking (Alg. 6), by every lane of the wave --------------
+    if (S == 1 ? !search : __ballot(search) == 0ull) continue;
+    wave_sync();
+    int taken = -1;
+    if constexpr (kMixed) {
+      if (__ballot(search && !hi) != 0ull) {
+        const int tk = wave_search<OBJ, G, G, TP, T>(L, hot, search && !hi, f, ddir, wave_lds, lay);
+        if (search && !hi) {
+          taken = tk;
+          if (tk < 0) {
+            ls_trials += hot.iter_ls;
+            hi = true;  // escalate: FP32 cannot resolve this decrease
+            fresh = true;
+            search = false;
+          }
+        }
+      }
+      if (__ballot(search && taken < 0) != 0ull) {
+        const bool need = search && taken < 0;
+        const int tk = wave_search<OBJ, G, G, TP, double>(L, hot, need, f, ddir, wave_lds, lay);
+        if (need) taken = tk;
+      }
+    } else {
+      taken = wave_search<OBJ, G, G, TP, double>(L, hot, search, f, ddir, wave_lds, lay);
     }
-    const int nshrink = taken >= 0 ? taken : q.iter_ls;
-    ls_trials += taken >= 0 ? taken + 1 : q.iter_ls;
-    const double alpha = step_length(sh.al, q.shrink, nshrink);
+    wave_sync();  // every lane has read xs in the line search
 
     // -- step: x_new = x + alpha p, s = x_new - x -----------------------------
-    const double xnew = xj + alpha * pj;
-    sj = own ? xnew - xj : 0.0;
-    xj = own ? xnew : 0.0;
-    wave_sync();  // every lane has read xs in the line search
-    sh.xs[j] = xj;
+    if (search) {
+      const int nshrink = taken >= 0 ? taken : hot.iter_ls;
+      ls_trials += taken >= 0 ? taken + 1 : hot.iter_ls;
+      const double alpha = step_length(sh.al, q.shrink, nshrink);
+      const double xnew = xj + alpha * pj;
+      sj = own ? xnew - xj : 0.0;
+      xj = own ? xnew : 0.0;
+      sh.xs[j] = xj;
+    }
   }
 }
 

@@ -192,7 +192,7 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
     else if (norm_below(gg, q.tol))
       status = ZEUS_ST_CONVERGED;
     else
-      status = budget_status(q, k, bound);
+      status = budget_status(q, q.iter_bfgs, k, bound);
     if (status >= 0) {
       const ReqDev &rq = reqs[q.ri];
       const int tl = q.trace_len;

@@ -232,7 +232,7 @@ __global__ __launch_bounds__(kWide) void bfgs_wide_kernel(const ReqDev *reqs, in
     else if (norm_below(gg, q.tol))
       status = ZEUS_ST_CONVERGED;
     else
-      status = budget_status(q, k, bound);
+      status = budget_status(q, q.iter_bfgs, k, bound);
     if (status >= 0) {
       const ReqDev &rq = reqs[q.ri];
       const int tl = q.trace_len;

@@ -460,10 +460,11 @@ struct Tile {
 
 // Value of the objective at the point whose coordinates are xs[0..d-1] in the
 // group's LDS, evaluated in number type T.  The group covers G * CPL term
-// slots: lane c evaluates the terms c, c + G, ..., c + (CPL-1) G (zero past
-// the last term); each block of G consecutive slots is summed by the lane
-// butterfly and the CPL block sums are added pairwise, which is the pairwise
-// tree over all G * CPL slots.  All lanes of the group must call it.
+// slots: lane c evaluates the terms CPL c .. CPL c + CPL - 1 (zero past the
+// last term) and adds them pairwise, the lane butterfly adds the lanes' sums,
+// which is the pairwise tree over all G * CPL slots.  (With the terms c,
+// c + G, ... in lane c, every block of G slots needs a butterfly of its own.)
+// All lanes of the group must call it.
 template <int OBJ, int G, int CPL, class T>
 __device__ __forceinline__ double group_value_slots(const GroupLanes<G> &L, int d,
                                                     const double *xs) {
@@ -475,18 +476,18 @@ __device__ __forceinline__ double group_value_slots(const GroupLanes<G> &L, int 
   T blk[E::K][CPL];
 #pragma unroll
   for (int r = 0; r < CPL; ++r) {
-    const int i = L.j + G * r;
+    const int i = CPL * L.j + r;
     // evaluated on every slot (index clamped), zero past the last term
     T w[E::W], out[E::K];
 #pragma unroll
     for (int q = 0; q < E::W; ++q) w[q] = (T)xs[i + q < G * CPL ? i + q : G * CPL - 1];
     E::template term<T>(w, out);
 #pragma unroll
-    for (int k = 0; k < E::K; ++k) blk[k][r] = lane_tree_sum<G, T>(i < m ? out[k] : T(0));
+    for (int k = 0; k < E::K; ++k) blk[k][r] = i < m ? out[k] : T(0);
   }
   T s[E::K];
 #pragma unroll
-  for (int k = 0; k < E::K; ++k) s[k] = reg_tree_sum<CPL, T>(blk[k]);
+  for (int k = 0; k < E::K; ++k) s[k] = lane_tree_sum<G, T>(reg_tree_sum<CPL, T>(blk[k]));
   return (double)E::template outer<T>(d, s);
   }
 }
