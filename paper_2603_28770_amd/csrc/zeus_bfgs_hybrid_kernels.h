@@ -346,9 +346,9 @@ void bfgs_hybrid_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t tot
     // -- Armijo backtracking (Alg. 6) ---------------------------------------
     int taken;
     if (hi) {
-      taken = block_armijo<OBJ, double, kHSlots>(sh, f, ddir, lsphase, &acc);
+      taken = block_armijo<OBJ, double, kHSlots>(sh, sh.xs, sh.ps, f, ddir, lsphase, &acc);
     } else {
-      taken = block_armijo<OBJ, T, kHSlots>(sh, f, ddir, lsphase, &acc);
+      taken = block_armijo<OBJ, T, kHSlots>(sh, sh.xs, sh.ps, f, ddir, lsphase, &acc);
       if (taken < 0) {
         ls_trials += q.iter_ls;
         hi = true;  // escalate: FP32 cannot resolve this decrease

@@ -15,14 +15,18 @@
 //    then the two quarters of a row are added through LDS, which is the
 //    pairwise tree over the eight blocks (the order of every other kernel);
 //    lane i of wavefronts w and w + 2 both end with row 64 (w & 1) + i;
-//  * lanes 0 .. 127 own the coordinates (x, g, p, s, y); the vectors the
-//    tiles read (y, g, u, s) go through LDS in the padded layout, written
-//    before a reduction whose barrier publishes them (six barriers per
-//    iteration with an update, plus one per line-search round: the value at
-//    a new iterate takes the accepted trial's term sums, block_eval);
-//  * gradient, sums, line search (four trials per round, one per wavefront),
-//    termination and retirement are those of the device-memory block kernel
-//    (zeus_block.h), with the term slots cut to 128;
+//  * every wavefront keeps all coordinates (lane l the coordinates 2 l and
+//    2 l + 1), forms value, gradient and sums for itself and exchanges vectors
+//    with its own lanes in its own LDS copies, so an iteration has three
+//    barriers: one after each product's quarters (u = H y and H_new g) and one
+//    per line-search round (four trials, one per wavefront).  With a coordinate per lane and
+//    every sum finished across the block it had seven.  The copies cost a
+//    second coordinate's gradient and repeated sums, which the barriers'
+//    waits outweighed: Rosenbrock d = 128, 16,384 starts 89.6 -> 83.8 ms,
+//    Styblinski-Tang 6.80 -> 6.29 ms; Ackley, whose gradient is dear, 2.07 ->
+//    2.19 ms.  Bound by VALU issue and by latency between the barriers;
+//  * a user objective's gradient is still formed once in the block, a
+//    coordinate per lane, with a barrier of its own;
 //  * starts are claimed as by the other kernels: first the block's own index,
 //    then an agent-scope work counter.
 // The control flow is uniform across the block (one start per block), so
@@ -39,33 +43,41 @@ constexpr int kQuarter = 64;                    // rows and columns of a wavefro
 constexpr int kTVec = tile_vec_len(kTDim);      // doubles of a padded operand vector
 static_assert(kTDim == 2 * kQuarter, "four wavefronts hold two by two quarters");
 
-struct TileShm {
+// A wavefront's own copy of the vectors its lanes exchange.
+struct TileWave {
   double xs[kTDim];  // iterate under evaluation (x, then x_new), zero past d
   double ps[kTDim];  // search direction
-  double vs[kTVec];  // y, operand of u = H y, padded layout
-  double gs[kTVec];  // g, operand of p = -H g, padded layout
+  double vs[kTVec];  // y, then g: operand of u = H y and p = -H g, padded layout
   double ss[kTVec];  // s = x_new - x, padded layout
   double us[kTVec];  // u = H y, padded layout
-  double part[kBlockWaves][kQuarter];  // each wavefront's products over its quarter
-  double red[2][3][kBlockWaves];       // [phase][sum][wave] partial sums
+};
+
+struct TileShm {
+  TileWave wv[kBlockWaves];
+  double part[2][kBlockWaves][kQuarter];  // each wavefront's products over its quarter (u, H g)
+  double gx[kTDim];                       // the gradient, lane by lane (whole-form objectives)
+  double red[1][1][kBlockWaves];          // (its extent is the number of wavefronts)
   double tsum[2 * kBlockWaves][kMaxSums];   // [phase * waves + wave][sum] line-search trials' term sums
   double al[kTabTrials];
   int pass[2][kBlockWaves];            // [phase][wave] line-search outcome
   StartCounts cnt;                     // update skips and direction resets (thread 0)
   unsigned long long got;
-  int bound;                           // early-stop bound of this iteration
+  int bound;                           // early-stop bound
   ReqHot q;
 };
 
-// Row products of H with the padded vector v (in LDS): lane i of wavefront w
-// returns row 64 (w & 1) + i, its quarter's sum plus the other quarter's
-// (the same bits in wavefronts w and w ^ 2: IEEE addition commutes).
-__device__ __forceinline__ double tile_block_matvec(const Tile<64> &H, const double *v, TileShm &sh,
-                                                    int lane, int w, int c0) {
-  const double mine = H.matvec_bcast(v[vpos<kTDim>(c0 + lane)]);
-  sh.part[w][lane] = mine;
+// Row products of H with the vector whose entries this wavefront left in v
+// (padded layout): rows 2 lane and 2 lane + 1 in r.  Every wavefront forms its
+// quarter's products; after the barrier each adds the two quarters of every
+// row for itself.  The two products of an iteration use a buffer each, so a
+// buffer is written again only after the barrier of the other.
+__device__ __forceinline__ void tile_block_matvec(const Tile<64> &H, const double *v, TileShm &sh,
+                                                  int buf, int lane, int w, int c0, double (&r)[2]) {
+  sh.part[buf][w][lane] = H.matvec_bcast(v[vpos<kTDim>(c0 + lane)]);
   __syncthreads();
-  return mine + sh.part[w ^ 2][lane];
+  const int hf = lane >> 5, i = (2 * lane) & 63;  // rows 2 lane, 2 lane + 1: half hf, place i, i + 1
+#pragma unroll
+  for (int c = 0; c < 2; ++c) r[c] = sh.part[buf][hf][i + c] + sh.part[buf][hf + 2][i + c];
 }
 
 // See the narrow kernel for the mixed-precision rules (T = float).
@@ -73,19 +85,21 @@ template <int OBJ, class T>
 __global__ __launch_bounds__(kBlockLanes) __attribute__((amdgpu_waves_per_eu(2)))
 void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total) {
   constexpr bool kMixed = sizeof(T) != sizeof(double);
+  constexpr bool kWhole = whole_form<Elem<OBJ>>::value;
   __shared__ TileShm sh;
-  const int j = threadIdx.x;  // coordinate of lanes below kTDim
-  const int lane = j & 63, w = j >> 6;
+  const GroupLanes<64> L;
+  const int j = threadIdx.x;
+  const int lane = j & 63, w = __builtin_amdgcn_readfirstlane(j >> 6);
   const int r0 = kQuarter * (w & 1), c0 = kQuarter * (w >> 1);  // this wavefront's quarter
-  const bool coord = j < kTDim;
-  const int ci = j & (kTDim - 1);  // row whose products this lane receives
+  const int j0 = 2 * lane;                                      // the lane's coordinates j0, j0 + 1
+  TileWave &wv = sh.wv[w];
   Tile<64> H;
-  int phase = 0, lsphase = 0;
+  int lsphase = 0;
   int acc = -1;  // slot of sh.tsum with the accepted trial's term sums (block_armijo), or -1
-  bool own = false, first = true, fresh = false, hi = !kMixed;
-  double xj = 0.0, gj = 0.0, pj = 0.0, sj = 0.0, f = 0.0;
+  bool first = true, fresh = false, hi = !kMixed;
+  double xj[2] = {0.0, 0.0}, gj[2] = {0.0, 0.0}, sj[2] = {0.0, 0.0}, f = 0.0;
   int64_t idx = -1;
-  int k = 0, ls_trials = 0;
+  int k = 0, ls_trials = 0, bound = 0;
   const int es_pass = es_pass_of(hdr);
   int claims = 0;  // starts claimed after the first (second early-stop pass; thread 0)
 
@@ -112,62 +126,78 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
       if (j == 0) {
         load_hot<OBJ>(sh.q, rq, ri, es_pass);
         sh.cnt = StartCounts{0, 0};
+        sh.bound = es_bound(sh.q);
       }
       fill_step_lengths(sh.al, rq.shrink, j, kBlockLanes);
-      own = j < d0;
-      xj = own ? rq.ws.x[idx * d0 + j] : 0.0;  // x <- swarm[i]
-      if (coord) sh.xs[j] = xj;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        xj[c] = j0 + c < d0 ? rq.ws.x[idx * d0 + j0 + c] : 0.0;  // x <- swarm[i]
+        wv.xs[j0 + c] = xj[c];
+      }
       k = 0;  // H <- I before the first product (below)
       ls_trials = 0;
       fresh = true;
       hi = !kMixed;
+      __syncthreads();  // the request and the bound are visible
+      bound = sh.bound;
     }
-    // the stopping bound, read early (its use is at the termination test) by
-    // one thread for the block: the bound falls while the kernel runs
-    if (j == 0) sh.bound = es_bound(sh.q);
-    __syncthreads();  // xs, the request and the bound are visible; earlier reads are done
+    wave_sync();
     const ReqHot &q = sh.q;
     const int d = q.d;
-    const int bound = sh.bound;
 
-    // -- value and gradient at xs -------------------------------------------
-    double gn, fn;
-    if (hi)
-      fn = block_eval<OBJ, double, true>(d, sh.xs, &gn, sh, phase, acc);
-    else
-      fn = block_eval<OBJ, T, true>(d, sh.xs, &gn, sh, phase, acc);
+    // -- value and gradient at xs, on every wavefront ---------------------------
+    double gn[2], fn;
+    if constexpr (kWhole) {
+      // user code of unknown cost: a pass per coordinate, once in the block
+      double g1[1];
+      if (hi)
+        fn = Elem<OBJ>::template value_grad<double>(wv.xs, d, j < d ? j : -1, &g1[0]);
+      else
+        fn = Elem<OBJ>::template value_grad<T>(wv.xs, d, j < d ? j : -1, &g1[0]);
+      if (j < kTDim) sh.gx[j] = j < d ? g1[0] : 0.0;
+      __syncthreads();
+      gn[0] = sh.gx[j0];
+      gn[1] = sh.gx[j0 + 1];
+    } else {
+      const double *known = acc >= 0 ? sh.tsum[acc] : nullptr;
+      if (hi)
+        fn = value_grad_slots<OBJ, 64, 2, double>(L, d, wv.xs, gn, known);
+      else
+        fn = value_grad_slots<OBJ, 64, 2, T>(L, d, wv.xs, gn, known);
+    }
     acc = -1;
 
-    // y's, g'g and the non-finite test in one reduction, whose barrier also
-    // publishes y and g for the products below; right after a claim or an
-    // escalation y's is not used
-    const double yj = gn - gj;  // zero beyond the dimension and on lanes >= kTDim
-    if (coord) {
-      sh.vs[vpos<kTDim>(j)] = yj;
-      sh.gs[vpos<kTDim>(j)] = gn;
-    }
-    const bool bad = (own && !__builtin_isfinite(gn)) || !__builtin_isfinite(fn);
-    double sums[3] = {yj * sj, gn * gn, bad ? 1.0 : 0.0};
-    block_tree_sums<3, double>(sums, sh, phase);
-    const double sy = sums[0], gg = sums[1];
-    const bool any_bad = sums[2] != 0.0;
+    // y's, g'g and the non-finite test; right after a claim or an escalation
+    // y's is not used
+    const double yj[2] = {gn[0] - gj[0], gn[1] - gj[1]};  // zero beyond the dimension
+    const double sy = slot_dot<64, 2>(yj, sj);
+    const double gg = slot_dot<64, 2>(gn, gn);
+    const bool bad = (j0 < d && !__builtin_isfinite(gn[0])) ||
+                     (j0 + 1 < d && !__builtin_isfinite(gn[1])) || !__builtin_isfinite(fn);
+    const bool any_bad = __ballot(bad) != 0ull;
 
     // -- after a step: u = H y and the rank-2 update --------------------------
     if (!fresh) {
       if (sy > 0.0) {  // curvature condition; skip the update otherwise
         const double rho = 1.0 / sy;
-        double uj = tile_block_matvec(H, sh.vs, sh, lane, w, c0);
-        uj = ci < d ? uj : 0.0;
-        if (coord) {  // published by the barrier of the next reduction
-          sh.us[vpos<kTDim>(j)] = uj;
-          sh.ss[vpos<kTDim>(j)] = sj;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) wv.vs[vpos<kTDim>(j0) + c] = yj[c];
+        wave_sync();
+        double uj[2];
+        tile_block_matvec(H, wv.vs, sh, 0, lane, w, c0, uj);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          uj[c] = j0 + c < d ? uj[c] : 0.0;
+          wv.us[vpos<kTDim>(j0) + c] = uj[c];
+          wv.ss[vpos<kTDim>(j0) + c] = sj[c];
         }
-        const double yu = block_tree_sum(coord ? yj * uj : 0.0, sh, phase);
+        const double yu = slot_dot<64, 2>(yj, uj);
         const double beta = (rho * rho) * yu + rho;
+        wave_sync();
         // H+ = H - rho (s u' + u s') + beta s s'   (u = H y); inf * 0 would
         // have reached the padding when a coefficient is not finite
-        if (!H.rank2_bcast(rho, beta, sh.us + vpos<kTDim>(r0), sh.ss + vpos<kTDim>(r0),
-                           sh.us[vpos<kTDim>(c0 + lane)], sh.ss[vpos<kTDim>(c0 + lane)], lane, 0.0,
+        if (!H.rank2_bcast(rho, beta, wv.us + vpos<kTDim>(r0), wv.ss + vpos<kTDim>(r0),
+                           wv.us[vpos<kTDim>(c0 + lane)], wv.ss[vpos<kTDim>(c0 + lane)], lane, 0.0,
                            0.0))
           H.restore_padding_at(lane, d, r0, c0);
       } else if (j == 0) {
@@ -175,15 +205,20 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
       }
       ++k;
     }
-    gj = gn;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) gj[c] = gn[c];
     f = fn;
     fresh = false;
-    if (q.trace_len && own && k < q.trace_len) reqs[q.ri].trace[(idx * q.trace_len + k) * d + j] = xj;
+    if (q.trace_len && w == 0 && k < q.trace_len)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        if (j0 + c < d) reqs[q.ri].trace[(idx * q.trace_len + k) * d + j0 + c] = xj[c];
 
     // -- termination: non-finite, ||g|| < Theta, budget ---------------------
     if (kMixed && !hi && (any_bad || norm_below(gg, 10.0 * q.tol))) {
       hi = true;  // escalate: re-evaluate this point in FP64
       fresh = true;
+      if constexpr (kWhole) __syncthreads();  // gx has been read
       continue;
     }
     int status = -1;
@@ -197,8 +232,15 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
       const ReqDev &rq = reqs[q.ri];
       const int tl = q.trace_len;
       if (status == ZEUS_ST_CONVERGED && q.es && j == 0) es_converged(q.es, k, q.iter_bfgs, q.es_c);
-      if (own) rq.out_x[idx * d + j] = xj;
-      if (kMixed && !hi) f = block_eval<OBJ, double, false>(d, sh.xs, nullptr, sh, phase);
+      if (kMixed && !hi) f = group_value_slots<OBJ, 64, 2, double>(L, d, wv.xs);
+      if (w == 0)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+          if (j0 + c < d) {
+            rq.out_x[idx * d + j0 + c] = xj[c];
+            for (int kk = k + 1; kk < tl; ++kk)
+              rq.trace[(idx * tl + kk) * d + j0 + c] = __builtin_nan("");
+          }
       if (j == 0) {
         rq.out_f[idx] = f;
         rq.out_iters[idx] = k;
@@ -207,9 +249,8 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
         if (rq.out_skips) rq.out_skips[idx] = sh.cnt.skips;
         if (rq.out_resets) rq.out_resets[idx] = sh.cnt.resets;
       }
-      if (tl && own)
-        for (int kk = k + 1; kk < tl; ++kk) rq.trace[(idx * tl + kk) * d + j] = __builtin_nan("");
       idx = -1;
+      __syncthreads();  // every wavefront is done with the request before the next claim
       continue;
     }
 
@@ -218,24 +259,36 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
     // rather than at the claim keeps the old tile's registers from being
     // live beside the new one's (the claim path rejoins the loop with H).
     if (k == 0) H.identity_at(lane, r0, c0);
-    const double hg = tile_block_matvec(H, sh.gs, sh, lane, w, c0);
-    pj = own ? -hg : 0.0;
-    if (coord) sh.ps[j] = pj;  // published by the barrier of the next reduction
-    double ddir = block_tree_sum(gj * pj, sh, phase);
+    wave_sync();  // the product of y has read vs
+#pragma unroll
+    for (int c = 0; c < 2; ++c) wv.vs[vpos<kTDim>(j0) + c] = gj[c];
+    wave_sync();
+    double pj[2];
+    tile_block_matvec(H, wv.vs, sh, 1, lane, w, c0, pj);
+#pragma unroll
+    for (int c = 0; c < 2; ++c) pj[c] = j0 + c < d ? -pj[c] : 0.0;
+    double ddir = slot_dot<64, 2>(gj, pj);
     if (!(ddir < 0.0)) {
       if (j == 0) ++sh.cnt.resets;
       H.identity_at(lane, r0, c0);
-      pj = own ? -gj : 0.0;
-      if (coord) sh.ps[j] = pj;
-      ddir = block_tree_sum(gj * pj, sh, phase);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) pj[c] = j0 + c < d ? -gj[c] : 0.0;
+      ddir = slot_dot<64, 2>(gj, pj);
     }
+#pragma unroll
+    for (int c = 0; c < 2; ++c) wv.ps[j0 + c] = pj[c];
+    wave_sync();
+    // the stopping bound for the next test, read by one thread for the block
+    // and published by the search's first barrier: the bound falls while the
+    // kernel runs
+    if (j == 0) sh.bound = es_bound(q);
 
     // -- Armijo backtracking (Alg. 6) ---------------------------------------
     int taken;
     if (hi) {
-      taken = block_armijo<OBJ, double, kTDim>(sh, f, ddir, lsphase, &acc);
+      taken = block_armijo<OBJ, double, kTDim>(sh, wv.xs, wv.ps, f, ddir, lsphase, &acc);
     } else {
-      taken = block_armijo<OBJ, T, kTDim>(sh, f, ddir, lsphase, &acc);
+      taken = block_armijo<OBJ, T, kTDim>(sh, wv.xs, wv.ps, f, ddir, lsphase, &acc);
       if (taken < 0) {
         ls_trials += q.iter_ls;
         hi = true;  // escalate: FP32 cannot resolve this decrease
@@ -243,16 +296,20 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
         continue;
       }
     }
+    bound = sh.bound;
     const int nshrink = taken >= 0 ? taken : q.iter_ls;
     ls_trials += taken >= 0 ? taken + 1 : q.iter_ls;
     const double alpha = step_length(sh.al, q.shrink, nshrink);
 
     // -- step: x_new = x + alpha p, s = x_new - x -----------------------------
-    // every lane has read xs and ps before the last barrier of the line search
-    const double xnew = xj + alpha * pj;
-    sj = own ? xnew - xj : 0.0;
-    xj = own ? xnew : 0.0;
-    if (coord) sh.xs[j] = xj;
+    wave_sync();  // the wavefront has read xs in its trials
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const double xnew = xj[c] + alpha * wv.ps[j0 + c];
+      sj[c] = j0 + c < d ? xnew - xj[c] : 0.0;
+      xj[c] = j0 + c < d ? xnew : 0.0;
+      wv.xs[j0 + c] = xj[c];
+    }
   }
 }
 

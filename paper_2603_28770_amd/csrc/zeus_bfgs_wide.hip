@@ -1,112 +1,199 @@
-// zeus_bfgs_wide.hip -- the BFGS phase with the inverse Hessian in device
-// memory (Alg. 4 / Alg. 10 with the dual-number gradient of Alg. 5 and the
-// Armijo search of Alg. 6): one block of 256 lanes per start.  It runs
-// 208 < d <= 256, where H no longer fits on chip, and any d > 64 when the
-// tiling is forced (ZEUS_TILE_LANES=256), which the tests use to compare it
-// with the on-chip kernels.
+// zeus_bfgs_wide.hip -- the BFGS phase for 208 < d <= 256 on gfx950 (Alg. 4 /
+// Alg. 10 with the dual-number gradient of Alg. 5 and the Armijo search of
+// Alg. 6): one block of eight wavefronts per start, the inverse Hessian spread
+// over registers, LDS and a device-memory slot of the block.
 //
-//  * lane i owns coordinate i and row i of the inverse Hessian H;
-//  * a row of up to 256 doubles does not fit in registers, so H lives in a
-//    slot of device memory owned by the block, stored column by column
-//    (element (i, c) at c * CS + i, CS = the dimension rounded up to 64):
-//    every pass over H reads or writes consecutive addresses across the
-//    lanes.  A block keeps its slot for every start it runs;
-//  * per iteration H is read once by u = H y and once more by the rank-2
-//    update, which writes the new rows and forms p = -H_new g_new from them in
-//    the same pass (the search direction needs no third pass);
-//  * a row's product with a vector is a fused multiply-add chain over each
-//    block of 16 consecutive columns, the block sums added pairwise (the
-//    order of the tile layout of the narrow kernel);
-//  * sums over coordinates and terms are the pairwise trees used everywhere:
-//    a butterfly inside each wavefront, then the four wavefront sums added
-//    pairwise through LDS;
-//  * the line search evaluates four trials per round, one per wavefront;
-//  * starts are claimed as by the narrow kernel: first the block's own index,
+//  * H is 256 x 256 (zero-padded past the dimension, ones on the padded
+//    diagonal), a 4 x 4 grid of 64 x 64 tiles.  512 KB are the whole register
+//    file of a CU, so it cannot stay there beside the rest of an iteration;
+//    wavefront w holds two tiles of rows 64 (w & 3) .. + 63: the one of
+//    columns 64 (w >> 2) .. + 63 in its registers, in the 4 x 16 lane tiles of
+//    the narrow kernel's 64-lane groups (zeus_group.h Tile), and the one 128
+//    columns to the right, a row per lane, as four strips of 16 columns:
+//    strips 0 and 1 in LDS (128 KB for the block), strips 2 and 3 in the slot
+//    (at most 128 KB a block, which the L2 and the last-level cache hold).
+//    Strips wholly in the padding are skipped.
+//  * Every wavefront keeps all coordinates (lane l the coordinates 4 l .. 4 l + 3)
+//    and evaluates value, gradient and sums for itself, so an iteration has
+//    three barriers: one after each product's partial sums (u = H y and
+//    H_new g) and one per line-search round (eight trials, one per wavefront).
+//    The vectors of an iteration are shared in LDS: all wavefronts write the
+//    same values, and a vector is written again only after a barrier that
+//    follows its last reader.
+//  * A row's product with a vector is a fused multiply-add chain over each
+//    block of 16 consecutive columns, the block sums added pairwise over the
+//    16 blocks (the order of every other kernel): each tile's four blocks meet
+//    in its wavefront, the four tiles of a row through LDS.
+//  * The strips are updated and multiplied by g in one pass.
+//  * Starts are claimed as by the other kernels: first the block's own index,
 //    then an agent-scope work counter.
 // The control flow is uniform across the block (one start per block), so
-// every barrier is reached by all its threads.
+// every barrier is reached by all its threads.  One block fills a CU's LDS.
+//
+// Bound by the strips' traffic and by latency between the barriers: per
+// iteration and block 128 KB of LDS and up to 128 KB of slot are read twice and written
+// once.  Rosenbrock d = 256, 509 starts: WIDE_FIGURES.
 #include "zeus_block.h"
 
 namespace zeus {
 namespace {
 
-constexpr int kWide = kBlockLanes;   // lanes (threads) per start
-constexpr int kWaves = kBlockWaves;  // wavefronts per start == trials per round
+constexpr int kWW = 8;                    // wavefronts per start
+constexpr int kWLanes = 64 * kWW;         // lanes per start
+constexpr int kWVec = tile_vec_len(256);  // doubles of a padded operand vector (vpos<256>)
+constexpr int kStripLds = 2;              // strips of a wavefront in LDS (the other two in the slot)
+// doubles of a wavefront's strips in the slot
+constexpr int kSlotWave = (4 - kStripLds) * 16 * 64;
 
-struct WideShm {
-  double xs[kWide];  // iterate under evaluation (x, then x_new)
-  double ps[kWide];  // search direction
-  double vs[kWide];  // y, operand of u = H y
-  double gs[kWide];  // gradient, operand of p = -H g
-  double ss[kWide];  // s = x_new - x
-  double us[kWide];  // u = H y
-  double red[2][2][kWaves];  // [phase][sum][wave] partial sums
-  double tsum[2 * kWaves][kMaxSums];  // [phase * waves + wave][sum] line-search trials' term sums
-  double al[kTabTrials];
-  int pass[2][kWaves];       // [phase][wave] line-search outcome
-  StartCounts cnt;           // update skips and direction resets (thread 0)
-  unsigned long long got;
-  int bound;                 // early-stop bound of this iteration
-  ReqHot q;
+struct alignas(16) Pair {
+  double a, b;  // two consecutive columns
 };
 
-// See the narrow kernel for the mixed-precision rules (T = float): FP32
-// evaluation with escalation to FP64 near the minimum, on a non-finite value
-// or on a failed FP32 line search; H, s, y, p, g'p and Armijo stay FP64.
-//
-// Row products: blocks of kHBlock columns, the block sums added over the
-// zero-padded pairwise tree of kHBlocks leaves.  The tree is folded as the
-// blocks complete, like a binary counter: s[l] holds the finished subtree of
-// 2^l blocks waiting for its right sibling.  The block index is the same on
-// every lane, so the branches are uniform and the column loops stay short.
-constexpr int kHBlock = 16;
-constexpr int kHBlocks = kMaxDim / kHBlock;
-static_assert(kHBlocks == 16, "the fold below has four levels");
+struct WideShm {
+  alignas(16) double xs[256];    // iterate under evaluation (x, then x_new), zero past d
+  alignas(16) double ps[256];    // search direction
+  alignas(16) double vs[kWVec];  // y, operand of u = H y, padded layout
+  alignas(16) double gs[kWVec];  // g, operand of p = -H g, padded layout
+  alignas(16) double ss[kWVec];  // s = x_new - x, padded layout
+  alignas(16) double us[kWVec];  // u = H y, padded layout
+  alignas(16) double part[2][4][256];  // [product][tile column][row] partial sums
+  double red[1][1][kWW];         // (its extent is the number of wavefronts)
+  double tsum[2 * kWW][kMaxSums];     // [phase * waves + wave][sum] line-search trials' term sums
+  double al[kTabTrials];
+  int pass[2][kWW];              // [phase][wave] line-search outcome
+  StartCounts cnt;               // update skips and direction resets (thread 0)
+  unsigned long long got;
+  int bound;                     // early-stop bound
+  ReqHot q;
+  // [wave][strip][column pair][row]; last, so that the fields above stay within
+  // reach of the 16-bit offsets of LDS instructions from one base
+  Pair hl[kWW][kStripLds][8][64];
+};
+static_assert(sizeof(WideShm) <= 160 * 1024, "the block's state fits the LDS of a CU");
 
-__device__ __forceinline__ void fold_block(double x, int b, double (&s)[4], double &total) {
-  if (!(b & 1)) { s[0] = x; return; }
-  x = s[0] + x;
-  if (!(b & 2)) { s[1] = x; return; }
-  x = s[1] + x;
-  if (!(b & 4)) { s[2] = x; return; }
-  x = s[2] + x;
-  if (!(b & 8)) { s[3] = x; return; }
-  total = s[3] + x;
-}
-
-// sum_c H(j, c) v[c] for the column-major row starting at hc
-__device__ __forceinline__ double slot_row_dot(const double *hc, int64_t cs, const double *v, int d) {
-  double s[4] = {0.0, 0.0, 0.0, 0.0}, total = 0.0;
-  int b = 0;
-  for (; b * kHBlock < d; ++b) {
-    const int c0 = b * kHBlock;
-    double acc = 0.0;
-    if (c0 + kHBlock <= d) {
-#pragma unroll
-      for (int k = 0; k < kHBlock; ++k) acc = __builtin_fma(hc[(int64_t)(c0 + k) * cs], v[c0 + k], acc);
-    } else {
-      for (int c = c0; c < d; ++c) acc = __builtin_fma(hc[(int64_t)c * cs], v[c], acc);
-    }
-    fold_block(acc, b, s, total);
+// The strips of a wavefront's second tile: strip s, column pair k of this
+// lane's row.
+struct Strips {
+  Pair *lds;   // this lane's entry of strip 0, pair 0 in LDS
+  Pair *slot;  // ... of strip kStripLds in the slot
+  int live;    // strips that hold a column below the dimension (0: none, or no such row)
+  __device__ __forceinline__ Pair *at(int s, int k) const {
+    return s < kStripLds ? lds + (s * 8 + k) * 64 : slot + ((s - kStripLds) * 8 + k) * 64;
   }
-  for (; b < kHBlocks; ++b) fold_block(0.0, b, s, total);
-  return total;
+};
+
+__device__ __forceinline__ void strips_identity(const Strips &t, int row, int c0) {
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+    if (s < t.live)
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const int c = c0 + 16 * s + 2 * k;
+        *t.at(s, k) = Pair{row == c ? 1.0 : 0.0, row == c + 1 ? 1.0 : 0.0};
+      }
 }
+
+// This lane's row of the second tile times a vector: vec is the padded vector
+// from the tile's first column; the four strips' chains added pairwise.  A
+// strip's eight pairs are loaded before the arithmetic of the strip before it
+// has to be done, so loads and chains overlap.
+__device__ __forceinline__ double strips_matvec(const Strips &t, const double *vec, int lane) {
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 3; s >= 0; --s)  // the slot's strips first
+    if (s < t.live) {
+      asm volatile("" ::: "memory");  // one strip's loads at a time: bounds the live registers
+      Pair h[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) h[k] = *t.at(s, k);
+      const double v = vec[18 * s + (lane & 15)];  // padded: strip s starts at 18 s
+      static_for<0, 8>([&](auto kk) {
+        constexpr int k = decltype(kk)::value;
+        fmac_bcast<2 * k>(acc[s], v, h[k].a);
+        fmac_bcast<2 * k + 1>(acc[s], v, h[k].b);
+      });
+    }
+  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+}
+
+// The rank-2 update of the second tile and its product with g in one pass:
+// element (r, c) by fma(e_r, s_c, fma(a_r, u_c, H_rc)); us, ss, gs are the padded
+// vectors from the tile's first column.  fin false: a or e is not finite and
+// the padding's columns get the identity back.
+__device__ __forceinline__ double strips_update_matvec(const Strips &t, const double *us,
+                                                       const double *ss, const double *gs, double a,
+                                                       double e, bool fin, int row, int c0, int d,
+                                                       int lane) {
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int s = 3; s >= 0; --s)
+    if (s < t.live) {
+      asm volatile("" ::: "memory");
+      Pair h[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) h[k] = *t.at(s, k);
+      const int o = 18 * s + (lane & 15);
+      const double u = us[o], sv = ss[o], g = gs[o];
+      static_for<0, 8>([&](auto kk) {
+        constexpr int k = decltype(kk)::value;
+        upd_bcast<2 * k>(h[k].a, u, sv, a, e);
+        upd_bcast<2 * k + 1>(h[k].b, u, sv, a, e);
+      });
+      if (!fin) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          const int c = c0 + 16 * s + 2 * k;
+          if (c >= d) h[k].a = row == c ? 1.0 : 0.0;
+          if (c + 1 >= d) h[k].b = row == c + 1 ? 1.0 : 0.0;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) *t.at(s, k) = h[k];
+      static_for<0, 8>([&](auto kk) {
+        constexpr int k = decltype(kk)::value;
+        fmac_bcast<2 * k>(acc[s], g, h[k].a);
+        fmac_bcast<2 * k + 1>(acc[s], g, h[k].b);
+      });
+    }
+  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+}
+
+// The sums of rows 4 lane .. + 3 over the four tile columns (all wavefronts).
+__device__ __forceinline__ void wide_rows(const WideShm &sh, int buf, int j0, double (&r)[4]) {
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int i = j0 + c;
+    r[c] = (sh.part[buf][0][i] + sh.part[buf][1][i]) + (sh.part[buf][2][i] + sh.part[buf][3][i]);
+  }
+}
+
+// See the narrow kernel for the mixed-precision rules (T = float).
 template <int OBJ, class T>
-__global__ __launch_bounds__(kWide) void bfgs_wide_kernel(const ReqDev *reqs, int nreq,
-                                                          BatchDev *hdr, int64_t total,
-                                                          double *hslots, int cs, int64_t slot) {
+__global__ __launch_bounds__(kWLanes) __attribute__((amdgpu_waves_per_eu(2)))
+void bfgs_wide_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total, double *slots,
+                      int64_t slot_doubles) {
   constexpr bool kMixed = sizeof(T) != sizeof(double);
   __shared__ WideShm sh;
+  const GroupLanes<64> L;
   const int j = threadIdx.x;
-  double *H = hslots + (int64_t)blockIdx.x * slot;  // column c of row j at H[c * cs + j]
-  int phase = 0, lsphase = 0;
+  const int lane = j & 63, w = __builtin_amdgcn_readfirstlane(j >> 6);
+  const int r0 = 64 * (w & 3), tq = w >> 2;  // the wavefront's rows, its register tile's column
+  const int c0 = 64 * tq, c1 = c0 + 128;     // first columns of its two tiles
+  const int row = r0 + lane;                 // this lane's row of the second tile
+  const int j0 = 4 * lane;                   // the lane's coordinates j0 .. j0 + 3
+  const int v0 = vpos<256>(j0);              // their place in a padded vector
+  Tile<64> H;
+  Strips st;
+  st.lds = &sh.hl[w][0][0][lane];
+  st.slot = reinterpret_cast<Pair *>(slots + (int64_t)blockIdx.x * slot_doubles + w * kSlotWave) + lane;
+  st.live = 0;
+  int lsphase = 0;
   int acc = -1;  // slot of sh.tsum with the accepted trial's term sums (block_armijo), or -1
-  bool own = false, first = true, fresh = false, hi = !kMixed;
-  double xj = 0.0, gj = 0.0, pj = 0.0, sj = 0.0, f = 0.0;
+  bool first = true, fresh = false, hi = !kMixed;
+  double xj[4] = {0.0, 0.0, 0.0, 0.0}, gj[4] = {0.0, 0.0, 0.0, 0.0};
+  double sj[4] = {0.0, 0.0, 0.0, 0.0}, f = 0.0;
   int64_t idx = -1;
-  int k = 0, ls_trials = 0;
-  bool have_p = false;  // p = -H g already formed by the update pass
+  int k = 0, ls_trials = 0, bound = 0;
   const int es_pass = es_pass_of(hdr);
   int claims = 0;  // starts claimed after the first (second early-stop pass; thread 0)
 
@@ -129,101 +216,109 @@ __global__ __launch_bounds__(kWide) void bfgs_wide_kernel(const ReqDev *reqs, in
         __syncthreads();  // every thread has read sh.got before the next claim writes it
         continue;
       }
-      const int d0 = rq.d;
+      const int d0 = __builtin_amdgcn_readfirstlane(rq.d);
       if (j == 0) {
         load_hot<OBJ>(sh.q, rq, ri, es_pass);
         sh.cnt = StartCounts{0, 0};
+        sh.bound = es_bound(sh.q);
       }
-      fill_step_lengths(sh.al, rq.shrink, j, kWide);
-      own = j < d0;
-      xj = own ? rq.ws.x[idx * d0 + j] : 0.0;  // x <- swarm[i]
-      sh.xs[j] = xj;
-      if (own)  // H <- I
-        for (int c = 0; c < d0; ++c) H[(int64_t)c * cs + j] = (c == j) ? 1.0 : 0.0;
+      fill_step_lengths(sh.al, rq.shrink, j, kWLanes);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        xj[c] = j0 + c < d0 ? rq.ws.x[idx * d0 + j0 + c] : 0.0;  // x <- swarm[i]
+        sh.xs[j0 + c] = xj[c];
+      }
+      st.live = r0 < d0 && c1 < d0 ? (d0 - c1 + 15) / 16 : 0;
+      if (st.live > 4) st.live = 4;
+      strips_identity(st, row, c1);  // H <- I (the register tile before the first product)
       k = 0;
       ls_trials = 0;
       fresh = true;
       hi = !kMixed;
-      have_p = false;
+      __syncthreads();  // the request and the bound are visible
+      bound = sh.bound;
     }
-    // the stopping bound, read early (its use is at the termination test) by
-    // one thread for the block: the bound falls while the kernel runs
-    if (j == 0) sh.bound = es_bound(sh.q);
-    __syncthreads();  // xs, the request and the bound are visible; earlier reads are done
+    wave_sync();
     const ReqHot &q = sh.q;
-    const int d = q.d;
-    const int bound = sh.bound;
+    const int d = __builtin_amdgcn_readfirstlane(q.d);
 
-    // -- value and gradient at xs -------------------------------------------
-    double gn, fn;
-    if (hi)
-      fn = block_eval<OBJ, double, true>(d, sh.xs, &gn, sh, phase, acc);
-    else
-      fn = block_eval<OBJ, T, true>(d, sh.xs, &gn, sh, phase, acc);
+    // -- value and gradient at xs, on every wavefront ---------------------------
+    double gn[4], fn;
+    {
+      const double *known = acc >= 0 ? sh.tsum[acc] : nullptr;
+      if (hi)
+        fn = value_grad_slots<OBJ, 64, 4, double>(L, d, sh.xs, gn, known);
+      else
+        fn = value_grad_slots<OBJ, 64, 4, T>(L, d, sh.xs, gn, known);
+    }
     acc = -1;
 
-    // -- after a step: y, u = H y, the rank-2 update and p = -H_new g_new ----
-    have_p = false;
-    if (!fresh) {
-      const double yj = gn - gj;
-      const double sy = block_tree_sum(yj * sj, sh, phase);
-      if (sy > 0.0) {
-        const double rho = 1.0 / sy;
-        sh.vs[j] = yj;
-        sh.gs[j] = gn;
-        __syncthreads();
-        const double uj = own ? slot_row_dot(H + j, cs, sh.vs, d) : 0.0;
-        const double yu = block_tree_sum(yj * uj, sh, phase);
-        sh.us[j] = uj;
-        sh.ss[j] = sj;
-        __syncthreads();
-        const double beta = (rho * rho) * yu + rho;
-        const double au = -rho * sj;
-        const double as = beta * sj - rho * uj;
-        // H+ = H - rho (s u' + u s') + beta s s'   (row j), then p_j = -(H+ g)_j
-        double total = 0.0;
-        if (own) {
-          double *hc = H + j;
-          double s[4] = {0.0, 0.0, 0.0, 0.0};
-          auto upd = [&](int c, double acc) {
-            const double hn =
-                __builtin_fma(as, sh.ss[c], __builtin_fma(au, sh.us[c], hc[(int64_t)c * cs]));
-            hc[(int64_t)c * cs] = hn;
-            return __builtin_fma(hn, sh.gs[c], acc);
-          };
-          int b = 0;
-          for (; b * kHBlock < d; ++b) {
-            const int c0 = b * kHBlock;
-            double acc = 0.0;
-            if (c0 + kHBlock <= d) {
+    // y's, g'g and the non-finite test; right after a claim or an escalation
+    // y's is not used
+    double yj[4];
+    bool bad = !__builtin_isfinite(fn);
 #pragma unroll
-              for (int k = 0; k < kHBlock; ++k) acc = upd(c0 + k, acc);
-            } else {
-              for (int c = c0; c < d; ++c) acc = upd(c, acc);
-            }
-            fold_block(acc, b, s, total);
-          }
-          for (; b < kHBlocks; ++b) fold_block(0.0, b, s, total);
+    for (int c = 0; c < 4; ++c) {
+      yj[c] = gn[c] - gj[c];  // zero beyond the dimension
+      bad = bad || (j0 + c < d && !__builtin_isfinite(gn[c]));
+      sh.vs[v0 + c] = yj[c];
+      sh.gs[v0 + c] = gn[c];
+    }
+    const double sy = slot_dot<64, 4>(yj, sj);
+    const double gg = slot_dot<64, 4>(gn, gn);
+    const bool any_bad = __ballot(bad) != 0ull;
+
+    // -- after a step: u = H y and the rank-2 update, the strips' part of the
+    //    product H_new g with it --------------------------------------------
+    bool updated = false;
+    if (!fresh) {
+      if (sy > 0.0) {  // curvature condition; skip the update otherwise
+        const double rho = 1.0 / sy;
+        wave_sync();
+        sh.part[0][tq + 2][row] = strips_matvec(st, sh.vs + vpos<256>(c1), lane);
+        sh.part[0][tq][row] = H.matvec_bcast(sh.vs[vpos<256>(c0 + lane)]);
+        __syncthreads();
+        double uj[4];
+        wide_rows(sh, 0, j0, uj);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          uj[c] = j0 + c < d ? uj[c] : 0.0;
+          sh.us[v0 + c] = uj[c];
+          sh.ss[v0 + c] = sj[c];
         }
-        pj = own ? -total : 0.0;
-        have_p = true;
+        const double yu = slot_dot<64, 4>(yj, uj);
+        const double beta = (rho * rho) * yu + rho;
+        wave_sync();
+        // H+ = H - rho (s u' + u s') + beta s s'   (u = H y); inf * 0 would
+        // have reached the padding when a coefficient is not finite
+        const double sr = sh.ss[vpos<256>(row)], ur = sh.us[vpos<256>(row)];
+        const double a = -rho * sr, e = beta * sr - rho * ur;
+        sh.part[1][tq + 2][row] = strips_update_matvec(
+            st, sh.us + vpos<256>(c1), sh.ss + vpos<256>(c1), sh.gs + vpos<256>(c1), a, e,
+            __builtin_isfinite(a) && __builtin_isfinite(e), row, c1, d, lane);
+        if (!H.rank2_bcast(rho, beta, sh.us + vpos<256>(r0), sh.ss + vpos<256>(r0),
+                           sh.us[vpos<256>(c0 + lane)], sh.ss[vpos<256>(c0 + lane)], lane, 0.0, 0.0))
+          H.restore_padding_at(lane, d, r0, c0);
+        updated = true;
       } else if (j == 0) {
         ++sh.cnt.skips;
       }
       ++k;
     }
-    gj = gn;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) gj[c] = gn[c];
     f = fn;
     fresh = false;
-    if (q.trace_len && own && k < q.trace_len) reqs[q.ri].trace[(idx * q.trace_len + k) * d + j] = xj;
+    if (q.trace_len && w == 0 && k < q.trace_len)
+#pragma unroll
+      for (int c = 0; c < 4; ++c)
+        if (j0 + c < d) reqs[q.ri].trace[(idx * q.trace_len + k) * d + j0 + c] = xj[c];
 
-    // -- termination ----------------------------------------------------------
-    const bool bad = (own && !__builtin_isfinite(gj)) || !__builtin_isfinite(f);
-    const bool any_bad = __syncthreads_or(bad) != 0;
-    const double gg = block_tree_sum(gj * gj, sh, phase);
+    // -- termination: non-finite, ||g|| < Theta, budget ---------------------
     if (kMixed && !hi && (any_bad || norm_below(gg, 10.0 * q.tol))) {
-      hi = true;
+      hi = true;  // escalate: re-evaluate this point in FP64
       fresh = true;
+      __syncthreads();  // every wavefront has read the vectors that are written again
       continue;
     }
     int status = -1;
@@ -237,8 +332,15 @@ __global__ __launch_bounds__(kWide) void bfgs_wide_kernel(const ReqDev *reqs, in
       const ReqDev &rq = reqs[q.ri];
       const int tl = q.trace_len;
       if (status == ZEUS_ST_CONVERGED && q.es && j == 0) es_converged(q.es, k, q.iter_bfgs, q.es_c);
-      if (own) rq.out_x[idx * d + j] = xj;
-      if (kMixed && !hi) f = block_eval<OBJ, double, false>(d, sh.xs, nullptr, sh, phase);
+      if (kMixed && !hi) f = group_value_slots<OBJ, 64, 4, double>(L, d, sh.xs);
+      if (w == 0)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          if (j0 + c < d) {
+            rq.out_x[idx * d + j0 + c] = xj[c];
+            for (int kk = k + 1; kk < tl; ++kk)
+              rq.trace[(idx * tl + kk) * d + j0 + c] = __builtin_nan("");
+          }
       if (j == 0) {
         rq.out_f[idx] = f;
         rq.out_iters[idx] = k;
@@ -247,52 +349,69 @@ __global__ __launch_bounds__(kWide) void bfgs_wide_kernel(const ReqDev *reqs, in
         if (rq.out_skips) rq.out_skips[idx] = sh.cnt.skips;
         if (rq.out_resets) rq.out_resets[idx] = sh.cnt.resets;
       }
-      if (tl && own)
-        for (int kk = k + 1; kk < tl; ++kk) rq.trace[(idx * tl + kk) * d + j] = __builtin_nan("");
       idx = -1;
+      __syncthreads();  // every wavefront is done with the request before the next claim
       continue;
     }
 
-    // -- search direction p = -H g (formed above after an update) ------------
-    if (!have_p) {
-      sh.gs[j] = gj;
-      __syncthreads();
-      pj = own ? -slot_row_dot(H + j, cs, sh.gs, d) : 0.0;
-    }
-    double ddir = block_tree_sum(gj * pj, sh, phase);
-    if (!(ddir < 0.0)) {  // not a descent direction: H <- I, p = -g
-      if (j == 0) ++sh.cnt.resets;
-      if (own)
-        for (int c = 0; c < d; ++c) H[(int64_t)c * cs + j] = (c == j) ? 1.0 : 0.0;
-      pj = own ? -gj : 0.0;
-      ddir = block_tree_sum(gj * pj, sh, phase);
-    }
-    sh.ps[j] = pj;
+    // -- search direction p = -H g (reset to -g if not a descent direction) -
+    // The register tile is the identity until the first update (k = 0);
+    // setting it here rather than at the claim keeps the old tile's registers
+    // from being live beside the new one's.
+    if (k == 0) H.identity_at(lane, r0, c0);
+    wave_sync();
+    if (!updated) sh.part[1][tq + 2][row] = strips_matvec(st, sh.gs + vpos<256>(c1), lane);
+    sh.part[1][tq][row] = H.matvec_bcast(sh.gs[vpos<256>(c0 + lane)]);
     __syncthreads();
+    double pj[4];
+    wide_rows(sh, 1, j0, pj);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) pj[c] = j0 + c < d ? -pj[c] : 0.0;
+    double ddir = slot_dot<64, 4>(gj, pj);
+    if (!(ddir < 0.0)) {
+      if (j == 0) ++sh.cnt.resets;
+      H.identity_at(lane, r0, c0);
+      strips_identity(st, row, c1);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) pj[c] = j0 + c < d ? -gj[c] : 0.0;
+      ddir = slot_dot<64, 4>(gj, pj);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sh.ps[j0 + c] = pj[c];
+    wave_sync();
+    // the stopping bound for the next test, read by one thread for the block
+    // and published by the search's first barrier: the bound falls while the
+    // kernel runs
+    if (j == 0) sh.bound = es_bound(q);
 
-    // -- Armijo backtracking -----------------------------------------------------
+    // -- Armijo backtracking (Alg. 6) ---------------------------------------
     int taken;
     if (hi) {
-      taken = block_armijo<OBJ, double, kWide>(sh, f, ddir, lsphase, &acc);
+      taken = block_armijo<OBJ, double, 256>(sh, sh.xs, sh.ps, f, ddir, lsphase, &acc);
     } else {
-      taken = block_armijo<OBJ, T, kWide>(sh, f, ddir, lsphase, &acc);
+      taken = block_armijo<OBJ, T, 256>(sh, sh.xs, sh.ps, f, ddir, lsphase, &acc);
       if (taken < 0) {
         ls_trials += q.iter_ls;
-        hi = true;
+        hi = true;  // escalate: FP32 cannot resolve this decrease
         fresh = true;
         continue;
       }
     }
+    bound = sh.bound;
     const int nshrink = taken >= 0 ? taken : q.iter_ls;
     ls_trials += taken >= 0 ? taken + 1 : q.iter_ls;
     const double alpha = step_length(sh.al, q.shrink, nshrink);
 
-    // -- step -------------------------------------------------------------------
-    const double xnew = xj + alpha * pj;
-    sj = own ? xnew - xj : 0.0;
-    xj = own ? xnew : 0.0;
-    __syncthreads();  // every lane has read xs and ps in the line search
-    sh.xs[j] = xj;
+    // -- step: x_new = x + alpha p, s = x_new - x -----------------------------
+    // x and p from the wavefront's own registers: another wavefront may have
+    // written the new x already
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const double xnew = xj[c] + alpha * pj[c];
+      sj[c] = j0 + c < d ? xnew - xj[c] : 0.0;
+      xj[c] = j0 + c < d ? xnew : 0.0;
+      sh.xs[j0 + c] = xj[c];
+    }
   }
 }
 
@@ -300,9 +419,9 @@ template <int OBJ, class T>
 hipError_t launch_wide_t(const Group &g, int64_t want, int cus) {
   int per_cu = 0;
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      &per_cu, reinterpret_cast<const void *>(&bfgs_wide_kernel<OBJ, T>), kWide, 0);
+      &per_cu, reinterpret_cast<const void *>(&bfgs_wide_kernel<OBJ, T>), kWLanes, 0);
   if (e != hipSuccess) return e;
-  if (per_cu < 1) per_cu = 1;
+  if (per_cu < 1) return hipErrorInvalidConfiguration;  // the block does not fit a CU
   int64_t cap = (int64_t)cus * per_cu;
   if (g.resident) {
     *g.resident = cap;
@@ -310,8 +429,8 @@ hipError_t launch_wide_t(const Group &g, int64_t want, int cus) {
   }
   if (cap > g.wide_slots) cap = g.wide_slots;
   const int blocks = (int)(want < cap ? want : cap);
-  hipLaunchKernelGGL((bfgs_wide_kernel<OBJ, T>), dim3(blocks), dim3(kWide), 0, g.stream, g.reqs,
-                     g.nreq, g.hdr, g.total_starts, g.hslots, g.wide_cs, g.wide_slot_doubles);
+  hipLaunchKernelGGL((bfgs_wide_kernel<OBJ, T>), dim3(blocks), dim3(kWLanes), 0, g.stream, g.reqs,
+                     g.nreq, g.hdr, g.total_starts, g.hslots, g.wide_slot_doubles);
   return hipGetLastError();
 }
 

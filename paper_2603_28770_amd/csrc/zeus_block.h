@@ -138,19 +138,17 @@ __device__ __forceinline__ double block_eval(int d, const double *xs, double *gj
 
 // One Armijo search (Alg. 6) with the objective in number type U over SLOTS
 // term slots (SLOTS a multiple of 64, at least the number of terms):
-// wavefront w of the NW evaluates trial base + w of each round; lane c of it
-// takes the term slots B c .. B c + B - 1 (B = SLOTS / 64) and adds them
-// pairwise, the wavefront finishes the pairwise sum.  Returns the index of the
+// wavefront w of the NW evaluates trial base + w of each round at the point
+// and direction it finds in xs and ps (LDS, zero past the dimension).  Returns the index of the
 // first passing trial, or -1.  *acc receives the slot of sh.tsum that holds
 // the passing trial's term sums (-1 when none passed or the objective has no
 // term structure); the slot is written again two rounds later, so it holds
 // until the next search's second round.
 template <int OBJ, class U, int SLOTS, class Shm>
-__device__ __forceinline__ int block_armijo(Shm &sh, double f, double ddir, int &lsphase,
-                                            int *acc) {
+__device__ __forceinline__ int block_armijo(Shm &sh, const double *xs, const double *ps, double f,
+                                            double ddir, int &lsphase, int *acc) {
   using E = Elem<OBJ>;
   static_assert(SLOTS % 64 == 0, "term slots come in whole wavefronts");
-  constexpr int B = SLOTS / 64;  // term slots per lane
   constexpr int NW = shm_waves<Shm>();
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const ReqHot &q = sh.q;
@@ -167,7 +165,7 @@ __device__ __forceinline__ int block_armijo(Shm &sh, double f, double ddir, int 
       bool ok = false;
       if (t < q.iter_ls) {
         const double alpha = step_length(sh.al, q.shrink, t);
-        ok = E::template trial<U>(sh.xs, sh.ps, alpha, d) <= f + (q.armijo_c * alpha) * ddir;
+        ok = E::template trial<U>(xs, ps, alpha, d) <= f + (q.armijo_c * alpha) * ddir;
       }
       const uint64_t hit = __ballot(ok);
       if (lane == 0) sh.pass[lsphase][w] = hit ? __ffsll((unsigned long long)hit) : 0;
@@ -184,27 +182,10 @@ __device__ __forceinline__ int block_armijo(Shm &sh, double f, double ddir, int 
   for (int base = 0; base < q.iter_ls; base += NW) {
     const int t = base + w;
     const double alpha = step_length(sh.al, q.shrink, t);
-    U tv[E::K][B];
-#pragma unroll
-    for (int b = 0; b < B; ++b) {
-      const int i = lane * B + b;
-      U out[E::K];
-#pragma unroll
-      for (int kk = 0; kk < E::K; ++kk) out[kk] = U(0);
-      if (i < m) {
-        U wv[E::W];
-#pragma unroll
-        for (int e = 0; e < E::W; ++e) wv[e] = (U)(sh.xs[i + e] + alpha * sh.ps[i + e]);
-        E::template term<U>(wv, out);
-      }
-#pragma unroll
-      for (int kk = 0; kk < E::K; ++kk) tv[kk][b] = out[kk];
-    }
+    const double bound = f + (q.armijo_c * alpha) * ddir;
     U sums[E::K];
-#pragma unroll
-    for (int kk = 0; kk < E::K; ++kk) sums[kk] = lane_tree_sum<64, U>(reg_tree_sum<B, U>(tv[kk]));
-    const double ft = (double)E::template outer<U>(d, sums);
-    const bool ok = t < q.iter_ls && ft <= f + (q.armijo_c * alpha) * ddir;
+    const double ft = trial_value<OBJ, SLOTS, 64, U>(xs, ps, alpha, d, m, lane, sums);
+    const bool ok = (t < q.iter_ls) & (ft <= bound);
     if (lane == 0) {
       sh.pass[lsphase][w] = ok ? 1 : 0;
 #pragma unroll

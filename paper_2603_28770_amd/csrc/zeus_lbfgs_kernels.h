@@ -41,97 +41,6 @@ __device__ __host__ __forceinline__ constexpr SearchLayout lbfgs_search_layout(i
   return SearchLayout{lbfgs_stride(slots), 0, slots, al, q, fd, fd + 2, acc};
 }
 
-// sum over the group's G * CPL coordinate slots of a[c] b[c] (pairwise).
-template <int G, int CPL>
-__device__ __forceinline__ double slot_dot(const double (&a)[CPL], const double (&b)[CPL]) {
-  double v[CPL];
-#pragma unroll
-  for (int c = 0; c < CPL; ++c) v[c] = a[c] * b[c];
-  return lane_tree_sum<G, double>(reg_tree_sum<CPL, double>(v));
-}
-
-// Value and gradient at xs in number type T for the lane's coordinates (see
-// group_value_grad: the same per-coordinate dual terms, the value summed over
-// all G * CPL term slots).
-//
-// known, when given (the same pointer on every lane of the group), holds in
-// the group's LDS the term sums of the line-search trial that produced xs
-// (wave_search): the same terms at the same point in the same number type
-// over the same pairwise tree of G * CPL slots, so they are the sums this
-// evaluation would form, and the value's butterflies are skipped (d = 200,
-// m = 8: 40.6 -> 39.5 ms).  In the BFGS lane-group kernel the same reuse saved
-// no time: there the value's butterfly overlaps other work.
-template <int OBJ, int G, int CPL, class T>
-__device__ __forceinline__ double value_grad_slots(const GroupLanes<G> &L, int d, const double *xs,
-                                                   double (&gj)[CPL], const double *known = nullptr) {
-  using E = Elem<OBJ>;
-  if constexpr (whole_form<E>::value) {
-    // Alg. 5 as written: for each of its coordinates the lane evaluates the
-    // function once on dual numbers seeded with that coordinate's e_j
-    double fv = 0.0;
-#pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-      const int jj = CPL * L.j + c;
-      double g;
-      fv = E::template value_grad<T>(xs, d, jj < d ? jj : -1, &g);
-      gj[c] = jj < d ? g : 0.0;
-    }
-    return fv;
-  } else {
-  static_assert(E::W <= 2, "the tangent sum assumes at most two terms per coordinate");
-  const int m = E::terms(d);
-  T val[E::K][CPL], tan[E::K][CPL];
-#pragma unroll
-  for (int c = 0; c < CPL; ++c) {
-    const int jj = CPL * L.j + c;
-#pragma unroll
-    for (int k = 0; k < E::K; ++k) {
-      tan[k][c] = T(0);
-      val[k][c] = T(0);
-    }
-    // evaluated on every lane (indices clamped), a missing term contributing
-    // an exact zero, so the loads are not behind branches
-#pragma unroll
-    for (int back = E::W - 1; back >= 0; --back) {
-      const int i = jj - back;
-      const bool valid = jj < d && i >= 0 && i < m;
-      dual<T> w[E::W], out[E::K];
-#pragma unroll
-      for (int q = 0; q < E::W; ++q) {
-        int iq = i + q < 0 ? 0 : i + q;
-        iq = iq < G * CPL ? iq : G * CPL - 1;
-        w[q] = dual<T>{(T)xs[iq], q == back ? T(1) : T(0)};
-      }
-      E::template term<dual<T>>(w, out);
-#pragma unroll
-      for (int k = 0; k < E::K; ++k) tan[k][c] = tan[k][c] + (valid ? out[k].t : T(0));
-      if (back == 0)
-#pragma unroll
-        for (int k = 0; k < E::K; ++k) val[k][c] = valid ? out[k].v : T(0);
-    }
-  }
-  T sv[E::K];
-  if (known) {
-#pragma unroll
-    for (int k = 0; k < E::K; ++k) sv[k] = (T)known[k];
-  } else {
-#pragma unroll
-    for (int k = 0; k < E::K; ++k) sv[k] = lane_tree_sum<G, T>(reg_tree_sum<CPL, T>(val[k]));
-  }
-  double fv = 0.0;
-#pragma unroll
-  for (int c = 0; c < CPL; ++c) {
-    dual<T> sd[E::K];
-#pragma unroll
-    for (int k = 0; k < E::K; ++k) sd[k] = dual<T>{sv[k], tan[k][c]};
-    const dual<T> r = E::template outer<dual<T>>(d, sd);
-    gj[c] = (CPL * L.j + c < d) ? (double)r.t : 0.0;
-    fv = (double)r.v;
-  }
-  return fv;
-  }
-}
-
 template <int OBJ, int G, int CPL, class T>
 __device__ __forceinline__ double value_slots(const GroupLanes<G> &L, int d, const double *xs) {
   return group_value_slots<OBJ, G, CPL, T>(L, d, xs);
