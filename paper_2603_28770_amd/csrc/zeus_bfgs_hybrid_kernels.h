@@ -8,19 +8,25 @@
 //    diagonal).  Rows and columns 0 .. 191 form a 3 x 3 grid of 64 x 64
 //    tiles; eight of them sit in the registers of the eight wavefronts, in
 //    the 4 x 16 lane tiles of the narrow kernel's 64-lane groups (zeus_group.h
-//    Tile).  The rest -- the ninth tile (rows and columns 128 .. 191), the
-//    column strip (rows 0 .. 191, columns 192 .. 207) and the row strip (rows
-//    192 .. 207, all columns) -- is held in LDS as chains of 16 consecutive
-//    columns of one row, 656 chains, element k of chain q at hl[k][q] so that
-//    the lanes of a wavefront read consecutive addresses; lane t owns chain t
-//    and lanes 0 .. 143 chain t + 512 as well;
+//    Tile).  The rest is held in LDS in units of 64 chains of 16 consecutive
+//    columns, a chain per lane: the ninth tile (rows and columns 128 .. 191)
+//    as four units of 16 rows, the row strip (rows 192 .. 207, columns
+//    0 .. 191) as three units of 64 columns, and the column strip (columns
+//    192 .. 207, all rows) as four units of 64 rows.  A wavefront holds one
+//    unit, the first three a second one;
 //  * a row's product with a vector is a fused multiply-add chain over each
 //    block of 16 consecutive columns, the block sums added pairwise over the
-//    13 blocks (the order of every other kernel): a register tile's four
-//    blocks meet in two lane-swap levels, the LDS chains are summed one per
-//    lane, and lane i < 208 adds row i's pieces in the tree's order;
-//  * chains that lie wholly in the padding are skipped: their products are
-//    exact zeros and the update leaves them as they are;
+//    13 blocks (the order of every other kernel): four blocks meet inside a
+//    wavefront in two lane-swap levels, whether of a register tile or of a
+//    unit, and lane i < 208 adds row i's four pieces;
+//  * a chain takes the vectors' entries of its columns by row broadcasts from
+//    the lanes' own entries, as the register tiles do, and its elements two at
+//    a time; the update and the product with the new gradient are one pass.
+//    (Every operand read from LDS, and the update and the product two passes,
+//    a chain took 128 LDS instructions per iteration instead of 28, and the LDS
+//    was what the iteration waited for: Rosenbrock, 2,048 starts, d = 200
+//    64.0 -> 47.1 ms, d = 160 45.1 -> 36.1 ms; Ackley d = 200, 4,096 starts 5.0 -> 4.3 ms.)
+//  * units that lie wholly in the padding are skipped;
 //  * lanes 0 .. 207 own the coordinates (x, g, p, s, y); the vectors the
 //    tiles and chains read go through LDS in the padded layout, written
 //    before a reduction whose barrier publishes them;
@@ -43,13 +49,15 @@ constexpr int kHW = 8;                     // wavefronts per start
 constexpr int kHLanes = 64 * kHW;          // lanes per start
 constexpr int kHB = kHD / 16;              // column blocks
 constexpr int kHReg = 192;                 // rows and columns of the 3 x 3 tile grid
-constexpr int kQT = 256;                   // chains of tile (2, 2): rows 128..191, blocks 8..11
-constexpr int kQC = kHReg;                 // column strip: rows 0..191, block 12
-constexpr int kQR = 16 * kHB;              // row strip: rows 192..207, blocks 0..12
-constexpr int kQ = kQT + kQC + kQR;        // chains in LDS
+constexpr int kUnits = 11;                 // units in LDS
+constexpr int kUnitRows = 4, kUnitCols = 7;  // first unit of the row strip, of the column strip
 constexpr int kHVec = tile_vec_len(256);   // doubles of a padded operand vector (vpos<256>)
 constexpr int kHSlots = 256;               // term slots of a line-search trial
 static_assert(kHD == kHReg + 16 && kHB == 13, "one 16-wide strip past the tile grid");
+
+struct alignas(16) ChainPair {
+  double a, b;  // two consecutive columns of a chain
+};
 
 struct HybridShm {
   double xs[kHSlots];            // iterate under evaluation (x, then x_new), zero past d
@@ -58,126 +66,167 @@ struct HybridShm {
   double gs[kHVec];              // g, operand of p = -H g, padded layout
   double ss[kHVec];              // s = x_new - x, padded layout
   double us[kHVec];              // u = H y, padded layout
-  double tpart[kHW][64];         // each wavefront's products over its register tile
-  double cpart[kQ];              // the chains' products
+  double part[4][kHSlots];       // [64-column piece][row] products (piece 3: the column strip)
   double red[2][3][kHW];         // [phase][sum][wave] partial sums
   double tsum[2 * kHW][kMaxSums];     // [phase * waves + wave][sum] line-search trials' term sums
   double al[kTabTrials];
   int pass[2][kHW];              // [phase][wave] line-search outcome
   StartCounts cnt;               // update skips and direction resets (thread 0)
-  int pad_hl[2];                 // places hl (below)
   unsigned long long got;
   int bound;                     // early-stop bound of this iteration
   ReqHot q;
   // last: the fields above stay within reach of the 16-bit offsets of LDS
   // instructions from one base, which keeps their addresses out of registers
-  double hl[16][kQ];             // the LDS part of H, element k of chain q at hl[k][q]
+  ChainPair hl[kUnits][8][64];   // the LDS part of H: [unit][column pair][lane]
 };
-// The chain array 8 bytes past a 16-byte boundary: 16-byte aligned, the
-// d = 200 solve took 2% longer (230.4 against 225.7 ms).
-static_assert(__builtin_offsetof(HybridShm, hl) % 16 == 8, "the chain array's placement in LDS");
 
-// Row and column block of chain q.
-__device__ __forceinline__ int chain_row(int q) {
-  return q < kQT ? 128 + (q & 63) : q < kQT + kQC ? q - kQT : kHReg + ((q - kQT - kQC) & 15);
-}
-__device__ __forceinline__ int chain_block(int q) {
-  return q < kQT ? 8 + (q >> 6) : q < kQT + kQC ? kHB - 1 : (q - kQT - kQC) >> 4;
-}
+// The chains of one unit: this lane's row and the columns of its chain.
+struct Unit {
+  ChainPair *h;  // column pair k at h[64 k]
+  int row, c0;   // the chain's row and first column
+  int piece;     // the 64-column piece of the row it belongs to
+  bool across;   // the four 16-lane rows hold four blocks of the same rows
+  bool live;     // some chain of the unit lies below the dimension
+};
 
-// The chains of lane t: t and t + 512, so lanes 0 .. 143 hold two.  The
-// wavefronts with the extra chains are the block's first ones: issue favours
-// a SIMD's older wavefronts, so there the longer path between two barriers is
-// served first.  Given instead to the wavefronts without gradient work (lanes
-// 256 .. 399) the same chains made the d = 200 solve 12% slower.
-// (A loop, not unrolled: two inlined copies of a chain's work would keep
-// both chains' loads in flight and spill.)
-template <class F>
-__device__ __forceinline__ void for_lane_chains(int t, F &&f) {
-#pragma unroll 1
-  for (int q = t; q < kQ; q += kHLanes) f(q);
-}
-
-// A chain with no row or no column below the dimension lies in the padding.
-__device__ __forceinline__ bool chain_live(int q, int d) {
-  return chain_row(q) < d && 16 * chain_block(q) < d;
-}
-
-// Identity entries of the LDS part (all chains).
-__device__ __forceinline__ void chains_identity(HybridShm &sh, int t) {
-  for_lane_chains(t, [&](int q) {
-    const int r = chain_row(q), c0 = 16 * chain_block(q);
-#pragma unroll
-    for (int k = 0; k < 16; ++k) sh.hl[k][q] = r == c0 + k ? 1.0 : 0.0;
-  });
-}
-
-// Row i of H v (lane i < kHD) from the register tiles' products (tpart) and
-// the chains' (cpart): the pairwise tree over the 13 blocks,
-// ((b0..b3 + b4..b7) + (b8..b11 + b12)).
-__device__ __forceinline__ double hybrid_row(const HybridShm &sh, int i) {
-  if (i < kHReg) {
-    const int a = i >> 6, l = i & 63;
-    const double t0 = sh.tpart[3 * a][l], t1 = sh.tpart[3 * a + 1][l];
-    const double t2 = a < 2 ? sh.tpart[3 * a + 2][l]
-                            : (sh.cpart[l] + sh.cpart[64 + l]) + (sh.cpart[128 + l] + sh.cpart[192 + l]);
-    return (t0 + t1) + (t2 + sh.cpart[kQT + i]);
+__device__ __forceinline__ Unit unit_of(HybridShm &sh, int u, int lane, int d) {
+  const int i = lane & 15, b = lane >> 4;
+  Unit t;
+  t.h = &sh.hl[u < kUnits ? u : 0][0][lane];
+  t.across = u < kUnitCols;
+  if (u < kUnitRows) {
+    t.row = 128 + 16 * u + i;
+    t.c0 = 128 + 16 * b;
+    t.piece = 2;
+    t.live = 128 + 16 * u < d;
+  } else if (u < kUnitCols) {
+    t.row = kHReg + i;
+    t.c0 = 64 * (u - kUnitRows) + 16 * b;
+    t.piece = u - kUnitRows;
+    t.live = kHReg < d;
+  } else {  // the last one holds 16 rows (the same in its four 16-lane rows)
+    t.row = u + 1 < kUnits ? 64 * (u - kUnitCols) + lane : kHReg + i;
+    t.c0 = kHReg;
+    t.piece = 3;
+    t.live = kHReg < d && u < kUnits;
   }
-  const double *c = sh.cpart + kQT + kQC + (i - kHReg);  // block b at c[16 b]
-  const double lo = ((c[0] + c[16]) + (c[32] + c[48])) + ((c[64] + c[80]) + (c[96] + c[112]));
-  const double hi = ((c[128] + c[144]) + (c[160] + c[176])) + c[192];
-  return lo + hi;
+  return t;
 }
 
-// H v for the padded vector vec (in LDS): every lane forms its register
-// tile's products and its chains' products, then lane i < kHD returns row i
-// (other lanes 0).
-__device__ __forceinline__ double hybrid_matvec(const Tile<64> &H, const double *vec, HybridShm &sh,
-                                                int t, int lane, int w, int c0, int d) {
-  sh.tpart[w][lane] = H.matvec_bcast(vec[vpos<256>(c0 + lane)]);
-  for_lane_chains(t, [&](int q) {
-    double acc = 0.0;
-    if (chain_live(q, d)) {
-      const double *v = vec + vpos<256>(16 * chain_block(q));  // 16 consecutive entries
-      // four columns at a time: a memory clobber between chunks keeps the
-      // next chunk's loads from being hoisted, which bounds the live registers
+// Place in a padded vector of the entry a lane holds for its chain's row
+// broadcasts: the chain's column at the lane's position in its row of 16.
+__device__ __forceinline__ int unit_entry(const Unit &t, int lane) {
+  return vpos<256>(t.c0) + (lane & 15);
+}
+
+// The wavefront's units: unit w, and unit w + 8 of the first three.  The
+// wavefronts with two are the block's first ones: issue favours a SIMD's
+// older wavefronts, so there the longer path between two barriers is served
+// first.
+template <class F>
+__device__ __forceinline__ void for_wave_units(HybridShm &sh, int w, int lane, int d, F &&f) {
+#pragma unroll 1
+  for (int u = w; u < kUnits; u += kHW) {
+    const Unit t = unit_of(sh, u, lane, d);
+    if (t.live) f(t);
+  }
+}
+
+__device__ __forceinline__ void units_identity(HybridShm &sh, int w, int lane, int d) {
+  for_wave_units(sh, w, lane, d, [&](const Unit &t) {
+    const int diag = Tile<64>::opaque(t.row - t.c0);
 #pragma unroll
-      for (int k0 = 0; k0 < 16; k0 += 4) {
-        if (k0 > 0) asm volatile("" ::: "memory");
-#pragma unroll
-        for (int k = k0; k < k0 + 4; ++k) acc = __builtin_fma(sh.hl[k][q], v[k], acc);
-      }
-    }
-    sh.cpart[q] = acc;
+    for (int k = 0; k < 8; ++k)
+      t.h[64 * k] = ChainPair{diag == 2 * k ? 1.0 : 0.0, diag == 2 * k + 1 ? 1.0 : 0.0};
   });
-  __syncthreads();
-  return t < kHD ? hybrid_row(sh, t) : 0.0;
 }
 
-// The rank-2 update of the chains (the register tiles update themselves):
-// element (r, c) by fma(e_r, s_c, fma(a_r, u_c, H_rc)), a_r = -rho s_r,
-// e_r = beta s_r - rho u_r; a chain whose coefficients are not finite gets
-// its padding back.
-__device__ __forceinline__ void chains_rank2(HybridShm &sh, int t, int d, double rho, double beta) {
-  for_lane_chains(t, [&](int q) {
-    if (!chain_live(q, d)) return;
-    const int r = chain_row(q), c0 = 16 * chain_block(q);
-    const double sr = sh.ss[vpos<256>(r)], ur = sh.us[vpos<256>(r)];
+// The unit's piece of its rows' products, from the lanes' chains.
+__device__ __forceinline__ void unit_piece(HybridShm &sh, const Unit &t, double acc) {
+  if (t.across) {
+    acc = half_pair_sum<16>(acc, acc);
+    acc = half_pair_sum<32>(acc, acc);
+  }
+  sh.part[t.piece][t.row] = acc;
+}
+
+// H v over the units, v the padded vector vec.
+__device__ __forceinline__ void units_matvec(HybridShm &sh, const double *vec, int w, int lane, int d) {
+  for_wave_units(sh, w, lane, d, [&](const Unit &t) {
+    const double v = vec[unit_entry(t, lane)];
+    double acc = 0.0;
+    static_for<0, 2>([&](auto hh) {
+      constexpr int k0 = 4 * decltype(hh)::value;
+      // four pairs at a time: a memory clobber keeps the next loads from
+      // being hoisted, which bounds the live registers
+      asm volatile("" ::: "memory");
+      ChainPair h[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) h[k] = t.h[64 * (k0 + k)];
+      static_for<0, 4>([&](auto kk) {
+        constexpr int k = decltype(kk)::value;
+        fmac_bcast<2 * (k0 + k)>(acc, v, h[k].a);
+        fmac_bcast<2 * (k0 + k) + 1>(acc, v, h[k].b);
+      });
+    });
+    unit_piece(sh, t, acc);
+  });
+}
+
+// The rank-2 update of the units (the register tiles update themselves) and
+// their product with g in one pass: element (r, c) by
+// fma(e_r, s_c, fma(a_r, u_c, H_rc)), a_r = -rho s_r, e_r = beta s_r - rho u_r; a
+// chain whose coefficients are not finite gets its padding back.
+__device__ __forceinline__ void units_update_matvec(HybridShm &sh, int w, int lane, int d, double rho,
+                                                    double beta) {
+  for_wave_units(sh, w, lane, d, [&](const Unit &t) {
+    const double sr = sh.ss[vpos<256>(t.row)], ur = sh.us[vpos<256>(t.row)];
     const double a = -rho * sr;
     const double e = beta * sr - rho * ur;
-    const double *uc = sh.us + vpos<256>(c0), *sc = sh.ss + vpos<256>(c0);
+    const bool fin = __builtin_isfinite(a) && __builtin_isfinite(e);
+    const int o = unit_entry(t, lane);
+    const double u = sh.us[o], s = sh.ss[o], g = sh.gs[o];
+    double acc = 0.0;
+    static_for<0, 2>([&](auto hh) {
+      constexpr int k0 = 4 * decltype(hh)::value;
+      asm volatile("" ::: "memory");
+      ChainPair h[4];
 #pragma unroll
-    for (int k0 = 0; k0 < 16; k0 += 4) {
-      if (k0 > 0) asm volatile("" ::: "memory");
+      for (int k = 0; k < 4; ++k) h[k] = t.h[64 * (k0 + k)];
+      static_for<0, 4>([&](auto kk) {
+        constexpr int k = decltype(kk)::value;
+        upd_bcast<2 * (k0 + k)>(h[k].a, u, s, a, e);
+        upd_bcast<2 * (k0 + k) + 1>(h[k].b, u, s, a, e);
+      });
+      if (!fin) {
+        const int c = Tile<64>::opaque(t.c0) + 2 * k0;
 #pragma unroll
-      for (int k = k0; k < k0 + 4; ++k)
-        sh.hl[k][q] = __builtin_fma(e, sc[k], __builtin_fma(a, uc[k], sh.hl[k][q]));
-    }
-    if (!(__builtin_isfinite(a) && __builtin_isfinite(e)))
+        for (int k = 0; k < 4; ++k) {
+          if (c + 2 * k >= d) h[k].a = t.row == c + 2 * k ? 1.0 : 0.0;
+          if (c + 2 * k + 1 >= d) h[k].b = t.row == c + 2 * k + 1 ? 1.0 : 0.0;
+        }
+      }
 #pragma unroll
-      for (int k = 0; k < 16; ++k)
-        if (c0 + k >= d) sh.hl[k][q] = r == c0 + k ? 1.0 : 0.0;
+      for (int k = 0; k < 4; ++k) t.h[64 * (k0 + k)] = h[k];
+      static_for<0, 4>([&](auto kk) {
+        constexpr int k = decltype(kk)::value;
+        fmac_bcast<2 * (k0 + k)>(acc, g, h[k].a);
+        fmac_bcast<2 * (k0 + k) + 1>(acc, g, h[k].b);
+      });
+    });
+    unit_piece(sh, t, acc);
   });
+}
+
+// Row t of the product whose pieces the wavefronts have written (lane t < kHD,
+// after the barrier): the pairwise tree over the 13 blocks,
+// ((b0..b3 + b4..b7) + (b8..b11 + b12)).  Pieces that hold no live column are
+// not written: rows take the first 64-column pieces that do.
+__device__ __forceinline__ double hybrid_row(const HybridShm &sh, int t, int d) {
+  if (t >= kHD) return 0.0;
+  const double lo = sh.part[0][t] + sh.part[1][t];
+  const double hi = kHReg < d ? sh.part[2][t] + sh.part[3][t] : sh.part[2][t];
+  return lo + hi;
 }
 
 // See the narrow kernel for the mixed-precision rules (T = float).
@@ -187,7 +236,7 @@ void bfgs_hybrid_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t tot
   constexpr bool kMixed = sizeof(T) != sizeof(double);
   __shared__ HybridShm sh;
   const int j = threadIdx.x;  // coordinate of lanes below kHD
-  const int lane = j & 63, w = j >> 6;
+  const int lane = j & 63, w = __builtin_amdgcn_readfirstlane(j >> 6);
   const int r0 = 64 * (w / 3), c0 = 64 * (w % 3);  // this wavefront's register tile
   const bool coord = j < kHD;
   Tile<64> H;
@@ -228,7 +277,7 @@ void bfgs_hybrid_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t tot
       own = j < d0;
       xj = own ? rq.ws.x[idx * d0 + j] : 0.0;  // x <- swarm[i]
       if (coord) sh.xs[j] = xj;
-      chains_identity(sh, j);  // H <- I (the register tiles before the first product)
+      units_identity(sh, w, lane, d0);  // H <- I (the register tiles before the first product)
       k = 0;
       ls_trials = 0;
       fresh = true;
@@ -265,10 +314,14 @@ void bfgs_hybrid_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t tot
     const bool any_bad = sums[2] != 0.0;
 
     // -- after a step: u = H y and the rank-2 update --------------------------
+    bool updated = false;
     if (!fresh) {
       if (sy > 0.0) {  // curvature condition; skip the update otherwise
         const double rho = 1.0 / sy;
-        double uj = hybrid_matvec(H, sh.vs, sh, j, lane, w, c0, d);
+        units_matvec(sh, sh.vs, w, lane, d);
+        sh.part[w % 3][r0 + lane] = H.matvec_bcast(sh.vs[vpos<256>(c0 + lane)]);
+        __syncthreads();
+        double uj = hybrid_row(sh, j, d);
         uj = own ? uj : 0.0;
         if (coord) {  // published by the barrier of the next reduction
           sh.us[vpos<256>(j)] = uj;
@@ -281,7 +334,8 @@ void bfgs_hybrid_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t tot
         if (!H.rank2_bcast(rho, beta, sh.us + vpos<256>(r0), sh.ss + vpos<256>(r0),
                            sh.us[vpos<256>(c0 + lane)], sh.ss[vpos<256>(c0 + lane)], lane, 0.0, 0.0))
           H.restore_padding_at(lane, d, r0, c0);
-        chains_rank2(sh, j, d, rho, beta);
+        units_update_matvec(sh, w, lane, d, rho, beta);  // and their pieces of H_new g
+        updated = true;
       } else if (j == 0) {
         ++sh.cnt.skips;
       }
@@ -330,14 +384,17 @@ void bfgs_hybrid_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t tot
     // setting them here rather than at the claim keeps the old tile's
     // registers from being live beside the new one's.
     if (k == 0) H.identity_at(lane, r0, c0);
-    const double hg = hybrid_matvec(H, sh.gs, sh, j, lane, w, c0, d);
+    if (!updated) units_matvec(sh, sh.gs, w, lane, d);
+    sh.part[w % 3][r0 + lane] = H.matvec_bcast(sh.gs[vpos<256>(c0 + lane)]);
+    __syncthreads();
+    const double hg = hybrid_row(sh, j, d);
     pj = own ? -hg : 0.0;
     if (coord) sh.ps[j] = pj;  // published by the barrier of the next reduction
     double ddir = block_tree_sum(gj * pj, sh, phase);
     if (!(ddir < 0.0)) {
       if (j == 0) ++sh.cnt.resets;
       H.identity_at(lane, r0, c0);
-      chains_identity(sh, j);
+      units_identity(sh, w, lane, d);
       pj = own ? -gj : 0.0;
       if (coord) sh.ps[j] = pj;
       ddir = block_tree_sum(gj * pj, sh, phase);
