@@ -11,7 +11,7 @@
 //    the narrow kernel's 64-lane groups (zeus_group.h Tile), and the one 128
 //    columns to the right, a row per lane, as four strips of 16 columns:
 //    strips 0 and 1 in LDS (128 KB for the block), strips 2 and 3 in the slot
-//    (at most 128 KB a block, which the L2 and the last-level cache hold).
+//    (at most 128 KB a block: 32 MB for the chip, which its caches hold).
 //    Strips wholly in the padding are skipped.
 //  * Every wavefront keeps all coordinates (lane l the coordinates 4 l .. 4 l + 3)
 //    and evaluates value, gradient and sums for itself, so an iteration has
@@ -31,8 +31,12 @@
 // every barrier is reached by all its threads.  One block fills a CU's LDS.
 //
 // Bound by the strips' traffic and by latency between the barriers: per
-// iteration and block 128 KB of LDS and up to 128 KB of slot are read twice and written
-// once.  Rosenbrock d = 256, 509 starts: WIDE_FIGURES.
+// iteration and block 128 KB of LDS and up to 128 KB of the slot are read twice
+// and written once.  With all of H in the slot, streamed from device memory,
+// Rosenbrock with 509 starts took 169 ms at d = 256 against 33.5 ms, 101 ms at
+// d = 209 against 23.6 ms, and with 2,048 starts 645 ms at d = 256 against 106 ms.
+// With a coordinate per lane and every sum finished across the block (seven
+// barriers, less arithmetic) d = 256 took 42.3 and 148 ms.
 #include "zeus_block.h"
 
 namespace zeus {
@@ -50,12 +54,13 @@ struct alignas(16) Pair {
 };
 
 struct WideShm {
-  alignas(16) double xs[256];    // iterate under evaluation (x, then x_new), zero past d
-  alignas(16) double ps[256];    // search direction
-  alignas(16) double vs[kWVec];  // y, operand of u = H y, padded layout
-  alignas(16) double gs[kWVec];  // g, operand of p = -H g, padded layout
-  alignas(16) double ss[kWVec];  // s = x_new - x, padded layout
-  alignas(16) double us[kWVec];  // u = H y, padded layout
+  // two buffers where the old vector is still read while the new one is
+  // written (x in the step, g for y)
+  alignas(16) double xs[2][256];    // iterate under evaluation (x, then x_new), zero past d
+  alignas(16) double ps[256];       // search direction
+  alignas(16) double gs[2][kWVec];  // g, operand of p = -H g, padded layout
+  alignas(16) double vs[kWVec];     // y, operand of u = H y, then u, padded layout
+  alignas(16) double ss[kWVec];     // s = x_new - x, padded layout
   alignas(16) double part[2][4][256];  // [product][tile column][row] partial sums
   double red[1][1][kWW];         // (its extent is the number of wavefronts)
   double tsum[2 * kWW][kMaxSums];     // [phase * waves + wave][sum] line-search trials' term sums
@@ -83,10 +88,11 @@ struct Strips {
 };
 
 __device__ __forceinline__ void strips_identity(const Strips &t, int row, int c0) {
+  row = Tile<64>::opaque(row);  // once per start: keeps the pattern out of registers
 #pragma unroll
   for (int s = 0; s < 4; ++s)
     if (s < t.live)
-#pragma unroll
+#pragma unroll 1
       for (int k = 0; k < 8; ++k) {
         const int c = c0 + 16 * s + 2 * k;
         *t.at(s, k) = Pair{row == c ? 1.0 : 0.0, row == c + 1 ? 1.0 : 0.0};
@@ -94,25 +100,29 @@ __device__ __forceinline__ void strips_identity(const Strips &t, int row, int c0
 }
 
 // This lane's row of the second tile times a vector: vec is the padded vector
-// from the tile's first column; the four strips' chains added pairwise.  A
-// strip's eight pairs are loaded before the arithmetic of the strip before it
-// has to be done, so loads and chains overlap.
+// from the tile's first column; the four strips' chains added pairwise.  The
+// pairs are loaded four at a time (a memory clobber keeps the next four from
+// being hoisted, which bounds the live registers).
 __device__ __forceinline__ double strips_matvec(const Strips &t, const double *vec, int lane) {
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int s = 3; s >= 0; --s)  // the slot's strips first
+  static_for<0, 4>([&](auto ss) {
+    constexpr int s = 3 - decltype(ss)::value;  // the slot's strips first
     if (s < t.live) {
-      asm volatile("" ::: "memory");  // one strip's loads at a time: bounds the live registers
-      Pair h[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) h[k] = *t.at(s, k);
       const double v = vec[18 * s + (lane & 15)];  // padded: strip s starts at 18 s
-      static_for<0, 8>([&](auto kk) {
-        constexpr int k = decltype(kk)::value;
-        fmac_bcast<2 * k>(acc[s], v, h[k].a);
-        fmac_bcast<2 * k + 1>(acc[s], v, h[k].b);
+      static_for<0, 2>([&](auto hh) {
+        constexpr int k0 = 4 * decltype(hh)::value;
+        asm volatile("" ::: "memory");
+        Pair h[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) h[k] = *t.at(s, k0 + k);
+        static_for<0, 4>([&](auto kk) {
+          constexpr int k = decltype(kk)::value;
+          fmac_bcast<2 * (k0 + k)>(acc[s], v, h[k].a);
+          fmac_bcast<2 * (k0 + k) + 1>(acc[s], v, h[k].b);
+        });
       });
     }
+  });
   return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
@@ -125,36 +135,41 @@ __device__ __forceinline__ double strips_update_matvec(const Strips &t, const do
                                                        double e, bool fin, int row, int c0, int d,
                                                        int lane) {
   double acc[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int s = 3; s >= 0; --s)
+  static_for<0, 4>([&](auto st) {
+    constexpr int s = 3 - decltype(st)::value;
     if (s < t.live) {
-      asm volatile("" ::: "memory");
-      Pair h[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) h[k] = *t.at(s, k);
       const int o = 18 * s + (lane & 15);
       const double u = us[o], sv = ss[o], g = gs[o];
-      static_for<0, 8>([&](auto kk) {
-        constexpr int k = decltype(kk)::value;
-        upd_bcast<2 * k>(h[k].a, u, sv, a, e);
-        upd_bcast<2 * k + 1>(h[k].b, u, sv, a, e);
-      });
-      if (!fin) {
+      static_for<0, 2>([&](auto hh) {
+        constexpr int k0 = 4 * decltype(hh)::value;
+        asm volatile("" ::: "memory");
+        Pair h[4];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const int c = c0 + 16 * s + 2 * k;
-          if (c >= d) h[k].a = row == c ? 1.0 : 0.0;
-          if (c + 1 >= d) h[k].b = row == c + 1 ? 1.0 : 0.0;
+        for (int k = 0; k < 4; ++k) h[k] = *t.at(s, k0 + k);
+        static_for<0, 4>([&](auto kk) {
+          constexpr int k = decltype(kk)::value;
+          upd_bcast<2 * (k0 + k)>(h[k].a, u, sv, a, e);
+          upd_bcast<2 * (k0 + k) + 1>(h[k].b, u, sv, a, e);
+        });
+        if (!fin) {
+          const int r = Tile<64>::opaque(row);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const int c = c0 + 16 * s + 2 * (k0 + k);
+            if (c >= d) h[k].a = r == c ? 1.0 : 0.0;
+            if (c + 1 >= d) h[k].b = r == c + 1 ? 1.0 : 0.0;
+          }
         }
-      }
 #pragma unroll
-      for (int k = 0; k < 8; ++k) *t.at(s, k) = h[k];
-      static_for<0, 8>([&](auto kk) {
-        constexpr int k = decltype(kk)::value;
-        fmac_bcast<2 * k>(acc[s], g, h[k].a);
-        fmac_bcast<2 * k + 1>(acc[s], g, h[k].b);
+        for (int k = 0; k < 4; ++k) *t.at(s, k0 + k) = h[k];
+        static_for<0, 4>([&](auto kk) {
+          constexpr int k = decltype(kk)::value;
+          fmac_bcast<2 * (k0 + k)>(acc[s], g, h[k].a);
+          fmac_bcast<2 * (k0 + k) + 1>(acc[s], g, h[k].b);
+        });
       });
     }
+  });
   return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 
@@ -190,8 +205,8 @@ void bfgs_wide_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
   int lsphase = 0;
   int acc = -1;  // slot of sh.tsum with the accepted trial's term sums (block_armijo), or -1
   bool first = true, fresh = false, hi = !kMixed;
-  double xj[4] = {0.0, 0.0, 0.0, 0.0}, gj[4] = {0.0, 0.0, 0.0, 0.0};
-  double sj[4] = {0.0, 0.0, 0.0, 0.0}, f = 0.0;
+  double f = 0.0;
+  int xb = 0, gb = 0;  // the buffers of xs and gs that hold the current x and g
   int64_t idx = -1;
   int k = 0, ls_trials = 0, bound = 0;
   const int es_pass = es_pass_of(hdr);
@@ -225,8 +240,8 @@ void bfgs_wide_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
       fill_step_lengths(sh.al, rq.shrink, j, kWLanes);
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        xj[c] = j0 + c < d0 ? rq.ws.x[idx * d0 + j0 + c] : 0.0;  // x <- swarm[i]
-        sh.xs[j0 + c] = xj[c];
+        sh.xs[xb][j0 + c] = j0 + c < d0 ? rq.ws.x[idx * d0 + j0 + c] : 0.0;  // x <- swarm[i]
+        sh.gs[gb][v0 + c] = sh.ss[v0 + c] = 0.0;
       }
       st.live = r0 < d0 && c1 < d0 ? (d0 - c1 + 15) / 16 : 0;
       if (st.live > 4) st.live = 4;
@@ -243,27 +258,31 @@ void bfgs_wide_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
     const int d = __builtin_amdgcn_readfirstlane(q.d);
 
     // -- value and gradient at xs, on every wavefront ---------------------------
+    const double *xs = sh.xs[xb];
     double gn[4], fn;
     {
       const double *known = acc >= 0 ? sh.tsum[acc] : nullptr;
       if (hi)
-        fn = value_grad_slots<OBJ, 64, 4, double>(L, d, sh.xs, gn, known);
+        fn = value_grad_slots<OBJ, 64, 4, double>(L, d, xs, gn, known);
       else
-        fn = value_grad_slots<OBJ, 64, 4, T>(L, d, sh.xs, gn, known);
+        fn = value_grad_slots<OBJ, 64, 4, T>(L, d, xs, gn, known);
     }
     acc = -1;
 
     // y's, g'g and the non-finite test; right after a claim or an escalation
     // y's is not used
-    double yj[4];
+    double yj[4], sj[4];
     bool bad = !__builtin_isfinite(fn);
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      yj[c] = gn[c] - gj[c];  // zero beyond the dimension
+      yj[c] = gn[c] - sh.gs[gb][v0 + c];  // zero beyond the dimension
+      sj[c] = sh.ss[v0 + c];
       bad = bad || (j0 + c < d && !__builtin_isfinite(gn[c]));
       sh.vs[v0 + c] = yj[c];
-      sh.gs[v0 + c] = gn[c];
+      sh.gs[gb ^ 1][v0 + c] = gn[c];
     }
+    gb ^= 1;
+    const double *gs = sh.gs[gb];
     const double sy = slot_dot<64, 4>(yj, sj);
     const double gg = slot_dot<64, 4>(gn, gn);
     const bool any_bad = __ballot(bad) != 0ull;
@@ -283,21 +302,20 @@ void bfgs_wide_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
           uj[c] = j0 + c < d ? uj[c] : 0.0;
-          sh.us[v0 + c] = uj[c];
-          sh.ss[v0 + c] = sj[c];
+          sh.vs[v0 + c] = uj[c];  // every wavefront has formed its products of y
         }
         const double yu = slot_dot<64, 4>(yj, uj);
         const double beta = (rho * rho) * yu + rho;
         wave_sync();
         // H+ = H - rho (s u' + u s') + beta s s'   (u = H y); inf * 0 would
         // have reached the padding when a coefficient is not finite
-        const double sr = sh.ss[vpos<256>(row)], ur = sh.us[vpos<256>(row)];
+        const double sr = sh.ss[vpos<256>(row)], ur = sh.vs[vpos<256>(row)];
         const double a = -rho * sr, e = beta * sr - rho * ur;
         sh.part[1][tq + 2][row] = strips_update_matvec(
-            st, sh.us + vpos<256>(c1), sh.ss + vpos<256>(c1), sh.gs + vpos<256>(c1), a, e,
+            st, sh.vs + vpos<256>(c1), sh.ss + vpos<256>(c1), gs + vpos<256>(c1), a, e,
             __builtin_isfinite(a) && __builtin_isfinite(e), row, c1, d, lane);
-        if (!H.rank2_bcast(rho, beta, sh.us + vpos<256>(r0), sh.ss + vpos<256>(r0),
-                           sh.us[vpos<256>(c0 + lane)], sh.ss[vpos<256>(c0 + lane)], lane, 0.0, 0.0))
+        if (!H.rank2_bcast(rho, beta, sh.vs + vpos<256>(r0), sh.ss + vpos<256>(r0),
+                           sh.vs[vpos<256>(c0 + lane)], sh.ss[vpos<256>(c0 + lane)], lane, 0.0, 0.0))
           H.restore_padding_at(lane, d, r0, c0);
         updated = true;
       } else if (j == 0) {
@@ -305,14 +323,12 @@ void bfgs_wide_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
       }
       ++k;
     }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) gj[c] = gn[c];
     f = fn;
     fresh = false;
     if (q.trace_len && w == 0 && k < q.trace_len)
 #pragma unroll
       for (int c = 0; c < 4; ++c)
-        if (j0 + c < d) reqs[q.ri].trace[(idx * q.trace_len + k) * d + j0 + c] = xj[c];
+        if (j0 + c < d) reqs[q.ri].trace[(idx * q.trace_len + k) * d + j0 + c] = xs[j0 + c];
 
     // -- termination: non-finite, ||g|| < Theta, budget ---------------------
     if (kMixed && !hi && (any_bad || norm_below(gg, 10.0 * q.tol))) {
@@ -332,12 +348,12 @@ void bfgs_wide_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
       const ReqDev &rq = reqs[q.ri];
       const int tl = q.trace_len;
       if (status == ZEUS_ST_CONVERGED && q.es && j == 0) es_converged(q.es, k, q.iter_bfgs, q.es_c);
-      if (kMixed && !hi) f = group_value_slots<OBJ, 64, 4, double>(L, d, sh.xs);
+      if (kMixed && !hi) f = group_value_slots<OBJ, 64, 4, double>(L, d, xs);
       if (w == 0)
 #pragma unroll
         for (int c = 0; c < 4; ++c)
           if (j0 + c < d) {
-            rq.out_x[idx * d + j0 + c] = xj[c];
+            rq.out_x[idx * d + j0 + c] = xs[j0 + c];
             for (int kk = k + 1; kk < tl; ++kk)
               rq.trace[(idx * tl + kk) * d + j0 + c] = __builtin_nan("");
           }
@@ -360,13 +376,16 @@ void bfgs_wide_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
     // from being live beside the new one's.
     if (k == 0) H.identity_at(lane, r0, c0);
     wave_sync();
-    if (!updated) sh.part[1][tq + 2][row] = strips_matvec(st, sh.gs + vpos<256>(c1), lane);
-    sh.part[1][tq][row] = H.matvec_bcast(sh.gs[vpos<256>(c0 + lane)]);
+    if (!updated) sh.part[1][tq + 2][row] = strips_matvec(st, gs + vpos<256>(c1), lane);
+    sh.part[1][tq][row] = H.matvec_bcast(gs[vpos<256>(c0 + lane)]);
     __syncthreads();
-    double pj[4];
+    double pj[4], gj[4];
     wide_rows(sh, 1, j0, pj);
 #pragma unroll
-    for (int c = 0; c < 4; ++c) pj[c] = j0 + c < d ? -pj[c] : 0.0;
+    for (int c = 0; c < 4; ++c) {
+      gj[c] = gs[v0 + c];
+      pj[c] = j0 + c < d ? -pj[c] : 0.0;
+    }
     double ddir = slot_dot<64, 4>(gj, pj);
     if (!(ddir < 0.0)) {
       if (j == 0) ++sh.cnt.resets;
@@ -387,9 +406,9 @@ void bfgs_wide_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
     // -- Armijo backtracking (Alg. 6) ---------------------------------------
     int taken;
     if (hi) {
-      taken = block_armijo<OBJ, double, 256>(sh, sh.xs, sh.ps, f, ddir, lsphase, &acc);
+      taken = block_armijo<OBJ, double, 256>(sh, xs, sh.ps, f, ddir, lsphase, &acc);
     } else {
-      taken = block_armijo<OBJ, T, 256>(sh, sh.xs, sh.ps, f, ddir, lsphase, &acc);
+      taken = block_armijo<OBJ, T, 256>(sh, xs, sh.ps, f, ddir, lsphase, &acc);
       if (taken < 0) {
         ls_trials += q.iter_ls;
         hi = true;  // escalate: FP32 cannot resolve this decrease
@@ -403,15 +422,13 @@ void bfgs_wide_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
     const double alpha = step_length(sh.al, q.shrink, nshrink);
 
     // -- step: x_new = x + alpha p, s = x_new - x -----------------------------
-    // x and p from the wavefront's own registers: another wavefront may have
-    // written the new x already
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
-      const double xnew = xj[c] + alpha * pj[c];
-      sj[c] = j0 + c < d ? xnew - xj[c] : 0.0;
-      xj[c] = j0 + c < d ? xnew : 0.0;
-      sh.xs[j0 + c] = xj[c];
+      const double x = xs[j0 + c], xnew = x + alpha * sh.ps[j0 + c];
+      sh.ss[v0 + c] = j0 + c < d ? xnew - x : 0.0;
+      sh.xs[xb ^ 1][j0 + c] = j0 + c < d ? xnew : 0.0;
     }
+    xb ^= 1;
   }
 }
 
