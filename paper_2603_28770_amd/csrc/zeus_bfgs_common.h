@@ -331,14 +331,17 @@ __device__ __forceinline__ int wave_search(const GroupLanes<G> &L, const HotRegs
   {
     do {
       const int t = base + r;
-      const double alpha = step_length(own + lay.al, oq.shrink, t);
+      // (whole form: lanes past the last trial take none, which spares them
+      // the step lengths past the table)
+      const bool tries = !whole_form<E>::value || t < iter_ls;
+      const double alpha = tries ? step_length(own + lay.al, oq.shrink, t) : 0.0;
       // the trial's bound, formed before the terms rather than behind them
       const double bound = f + (hot.armijo_c * alpha) * ddir;
       double ft = 0.0;
       U sums[E::K];
       if constexpr (whole_form<E>::value) {
         // a group that has not searched yet has no request in its slice
-        if (open) ft = E::template trial<U>(own + lay.xs, own + lay.ps, alpha, oq.d);
+        if (open & tries) ft = E::template trial<U>(own + lay.xs, own + lay.ps, alpha, oq.d);
       } else {
         ft = trial_value<OBJ, SLOTS, TP, U>(own + lay.xs, own + lay.ps, alpha, oq.d, oq.m, c, sums);
       }
@@ -386,13 +389,14 @@ __device__ __forceinline__ int wave_search(const GroupLanes<G> &L, const HotRegs
       double *sl = wave_lds + target * lay.stride;  // the slice of the group the lane works for
       const ReqHot &q = *reinterpret_cast<const ReqHot *>(sl + lay.q);
       const int t = base + ((lane / TP) & (per - 1));
-      const double alpha = step_length(sl + lay.al, q.shrink, t);
       const int target_ls = q.iter_ls;
+      const bool tries = !whole_form<E>::value || t < target_ls;
+      const double alpha = tries ? step_length(sl + lay.al, q.shrink, t) : 0.0;
       const double bound = sl[lay.fd] + (q.armijo_c * alpha) * sl[lay.fd + 1];
       double ft = 0.0;
       U sums[E::K];
       if constexpr (whole_form<E>::value) {
-        if (valid) ft = E::template trial<U>(sl + lay.xs, sl + lay.ps, alpha, q.d);
+        if (valid & tries) ft = E::template trial<U>(sl + lay.xs, sl + lay.ps, alpha, q.d);
       } else {
         ft = trial_value<OBJ, SLOTS, TP, U>(sl + lay.xs, sl + lay.ps, alpha, q.d, q.m, c, sums);
       }

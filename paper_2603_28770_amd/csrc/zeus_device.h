@@ -145,30 +145,36 @@ __device__ __forceinline__ double cos_taylor(double r) {  // |r| <= pi/4, to r^1
   return __builtin_fma(z, q, 1.0);
 }
 
+// v with its sign changed when bit 1 of q2 is set (q2 is 0 or 2).
+__device__ __forceinline__ double flip_sign(double v, int q2) {
+  return __builtin_bit_cast(double, __builtin_bit_cast(uint64_t, v) ^ ((uint64_t)(uint32_t)q2 << 62));
+}
+
 // x = k pi/2 + r for |x| < 2^48, where k = rint(x 2/pi) is the nearest
 // integer and each fused step rounds at the remainder's magnitude (accurate to
 // about an ulp of 1); from 2^48 on, and for non-finite x, sin and cos are NaN.
 // No library call: its large-argument reduction would raise the register
 // use of every kernel this is inlined into.
 __device__ __forceinline__ void sincos(double x, double &s, double &c) {
-  if (!(__builtin_fabs(x) < kTrigMax)) {
-    s = c = __builtin_nan("");
-    return;
-  }
+  // no branch: outside the range the remainder is meaningless and the results
+  // are replaced at the end
+  const bool in = __builtin_fabs(x) < kTrigMax;
   const double k = __builtin_rint(x * kTwoOverPi);  // x = k pi/2 + r
   double r = __builtin_fma(-k, kPio2A, x);
   r = __builtin_fma(-k, kPio2B, r);
   r = __builtin_fma(-k, kPio2C, r);
   const double sr = sin_taylor(r), cr = cos_taylor(r);
   const int q = (int)(k - 4.0 * __builtin_floor(k * 0.25));
-  s = (q == 0) ? sr : (q == 1) ? cr : (q == 2) ? -sr : -cr;
-  c = (q == 0) ? cr : (q == 1) ? -sr : (q == 2) ? -cr : sr;
+  // odd quarters swap sine and cosine; the signs are bit 1 of q and of q + 1
+  const double sq = (q & 1) ? cr : sr, cq = (q & 1) ? sr : cr;
+  const double nan = __builtin_nan("");
+  s = in ? flip_sign(sq, q & 2) : nan;
+  c = in ? flip_sign(cq, (q + 1) & 2) : nan;
 }
 
 __device__ __forceinline__ double exp(double x) {
-  if (x != x) return x;
-  if (x > 710.0) return __builtin_huge_val();
-  if (x < -746.0) return 0.0;
+  // no branch: outside the range the polynomial is meaningless and the result
+  // is replaced at the end
   const double k = __builtin_rint(x * kLog2e);  // x = k ln2 + r
   double r = __builtin_fma(-k, kLn2A, x);
   r = __builtin_fma(-k, kLn2B, r);
@@ -186,7 +192,9 @@ __device__ __forceinline__ double exp(double x) {
   p = __builtin_fma(p, r, 0.5);
   p = __builtin_fma(p, r, 1.0);
   p = __builtin_fma(p, r, 1.0);
-  return __builtin_ldexp(p, (int)k);
+  // NaN compares false and keeps its k, remainder and polynomial NaN
+  const double e = __builtin_ldexp(p, (int)k);
+  return x > 710.0 ? __builtin_huge_val() : x < -746.0 ? 0.0 : e;
 }
 }  // namespace zm
 
