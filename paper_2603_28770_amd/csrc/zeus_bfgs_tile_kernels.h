@@ -16,15 +16,19 @@
 //    pairwise tree over the eight blocks (the order of every other kernel);
 //    lane i of wavefronts w and w + 2 both end with row 64 (w & 1) + i;
 //  * every wavefront keeps all coordinates (lane l the coordinates 2 l and
-//    2 l + 1), forms value, gradient and sums for itself and exchanges vectors
-//    with its own lanes in its own LDS copies, so an iteration has three
-//    barriers: one after each product's quarters (u = H y and H_new g) and one
-//    per line-search round (four trials, one per wavefront).  With a coordinate per lane and
-//    every sum finished across the block it had seven.  The copies cost a
-//    second coordinate's gradient and repeated sums, which the barriers'
-//    waits outweighed: Rosenbrock d = 128, 16,384 starts 89.6 -> 83.8 ms,
-//    Styblinski-Tang 6.80 -> 6.29 ms; Ackley, whose gradient is dear, 2.07 ->
-//    2.19 ms.  Bound by VALU issue and by latency between the barriers;
+//    2 l + 1) and forms value, gradient and sums for itself, so an iteration
+//    has three barriers: one after each product's quarters (u = H y and
+//    H_new g) and one per line-search round (four trials, one per wavefront).
+//    The vectors the lanes exchange are shared in LDS: all wavefronts write
+//    the same values, and a vector is written again only after a barrier that
+//    follows its last reader (a copy per wavefront cost a user objective, which
+//    reads the whole point for every coordinate, 13%).  With a coordinate per
+//    lane and every sum finished across the block an iteration had seven
+//    barriers; the second coordinate's gradient and the repeated sums cost
+//    less than they did: Rosenbrock d = 128, 16,384 starts 89.7 -> 83.8 ms,
+//    Styblinski-Tang 6.84 -> 6.37 ms, Ackley d = 128, 8,192 starts 2.10 -> 1.92 ms
+//    (with the sine and cosine's branches gone).  Bound by VALU issue and by
+//    latency between the barriers;
 //  * a user objective's gradient is still formed once in the block, a
 //    coordinate per lane, with a barrier of its own;
 //  * starts are claimed as by the other kernels: first the block's own index,
@@ -43,17 +47,12 @@ constexpr int kQuarter = 64;                    // rows and columns of a wavefro
 constexpr int kTVec = tile_vec_len(kTDim);      // doubles of a padded operand vector
 static_assert(kTDim == 2 * kQuarter, "four wavefronts hold two by two quarters");
 
-// A wavefront's own copy of the vectors its lanes exchange.
-struct TileWave {
+struct TileShm {
   double xs[kTDim];  // iterate under evaluation (x, then x_new), zero past d
   double ps[kTDim];  // search direction
   double vs[kTVec];  // y, then g: operand of u = H y and p = -H g, padded layout
   double ss[kTVec];  // s = x_new - x, padded layout
   double us[kTVec];  // u = H y, padded layout
-};
-
-struct TileShm {
-  TileWave wv[kBlockWaves];
   double part[2][kBlockWaves][kQuarter];  // each wavefront's products over its quarter (u, H g)
   double gx[kTDim];                       // the gradient, lane by lane (whole-form objectives)
   double red[1][1][kBlockWaves];          // (its extent is the number of wavefronts)
@@ -92,7 +91,6 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
   const int lane = j & 63, w = __builtin_amdgcn_readfirstlane(j >> 6);
   const int r0 = kQuarter * (w & 1), c0 = kQuarter * (w >> 1);  // this wavefront's quarter
   const int j0 = 2 * lane;                                      // the lane's coordinates j0, j0 + 1
-  TileWave &wv = sh.wv[w];
   Tile<64> H;
   int lsphase = 0;
   int acc = -1;  // slot of sh.tsum with the accepted trial's term sums (block_armijo), or -1
@@ -132,7 +130,7 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         xj[c] = j0 + c < d0 ? rq.ws.x[idx * d0 + j0 + c] : 0.0;  // x <- swarm[i]
-        wv.xs[j0 + c] = xj[c];
+        sh.xs[j0 + c] = xj[c];
       }
       k = 0;  // H <- I before the first product (below)
       ls_trials = 0;
@@ -151,9 +149,9 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
       // user code of unknown cost: a pass per coordinate, once in the block
       double g1[1];
       if (hi)
-        fn = Elem<OBJ>::template value_grad<double>(wv.xs, d, j < d ? j : -1, &g1[0]);
+        fn = Elem<OBJ>::template value_grad<double>(sh.xs, d, j < d ? j : -1, &g1[0]);
       else
-        fn = Elem<OBJ>::template value_grad<T>(wv.xs, d, j < d ? j : -1, &g1[0]);
+        fn = Elem<OBJ>::template value_grad<T>(sh.xs, d, j < d ? j : -1, &g1[0]);
       if (j < kTDim) sh.gx[j] = j < d ? g1[0] : 0.0;
       __syncthreads();
       gn[0] = sh.gx[j0];
@@ -161,9 +159,9 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
     } else {
       const double *known = acc >= 0 ? sh.tsum[acc] : nullptr;
       if (hi)
-        fn = value_grad_slots<OBJ, 64, 2, double>(L, d, wv.xs, gn, known);
+        fn = value_grad_slots<OBJ, 64, 2, double>(L, d, sh.xs, gn, known);
       else
-        fn = value_grad_slots<OBJ, 64, 2, T>(L, d, wv.xs, gn, known);
+        fn = value_grad_slots<OBJ, 64, 2, T>(L, d, sh.xs, gn, known);
     }
     acc = -1;
 
@@ -181,23 +179,23 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
       if (sy > 0.0) {  // curvature condition; skip the update otherwise
         const double rho = 1.0 / sy;
 #pragma unroll
-        for (int c = 0; c < 2; ++c) wv.vs[vpos<kTDim>(j0) + c] = yj[c];
+        for (int c = 0; c < 2; ++c) sh.vs[vpos<kTDim>(j0) + c] = yj[c];
         wave_sync();
         double uj[2];
-        tile_block_matvec(H, wv.vs, sh, 0, lane, w, c0, uj);
+        tile_block_matvec(H, sh.vs, sh, 0, lane, w, c0, uj);
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
           uj[c] = j0 + c < d ? uj[c] : 0.0;
-          wv.us[vpos<kTDim>(j0) + c] = uj[c];
-          wv.ss[vpos<kTDim>(j0) + c] = sj[c];
+          sh.us[vpos<kTDim>(j0) + c] = uj[c];
+          sh.ss[vpos<kTDim>(j0) + c] = sj[c];
         }
         const double yu = slot_dot<64, 2>(yj, uj);
         const double beta = (rho * rho) * yu + rho;
         wave_sync();
         // H+ = H - rho (s u' + u s') + beta s s'   (u = H y); inf * 0 would
         // have reached the padding when a coefficient is not finite
-        if (!H.rank2_bcast(rho, beta, wv.us + vpos<kTDim>(r0), wv.ss + vpos<kTDim>(r0),
-                           wv.us[vpos<kTDim>(c0 + lane)], wv.ss[vpos<kTDim>(c0 + lane)], lane, 0.0,
+        if (!H.rank2_bcast(rho, beta, sh.us + vpos<kTDim>(r0), sh.ss + vpos<kTDim>(r0),
+                           sh.us[vpos<kTDim>(c0 + lane)], sh.ss[vpos<kTDim>(c0 + lane)], lane, 0.0,
                            0.0))
           H.restore_padding_at(lane, d, r0, c0);
       } else if (j == 0) {
@@ -232,7 +230,7 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
       const ReqDev &rq = reqs[q.ri];
       const int tl = q.trace_len;
       if (status == ZEUS_ST_CONVERGED && q.es && j == 0) es_converged(q.es, k, q.iter_bfgs, q.es_c);
-      if (kMixed && !hi) f = group_value_slots<OBJ, 64, 2, double>(L, d, wv.xs);
+      if (kMixed && !hi) f = group_value_slots<OBJ, 64, 2, double>(L, d, sh.xs);
       if (w == 0)
 #pragma unroll
         for (int c = 0; c < 2; ++c)
@@ -261,10 +259,10 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
     if (k == 0) H.identity_at(lane, r0, c0);
     wave_sync();  // the product of y has read vs
 #pragma unroll
-    for (int c = 0; c < 2; ++c) wv.vs[vpos<kTDim>(j0) + c] = gj[c];
+    for (int c = 0; c < 2; ++c) sh.vs[vpos<kTDim>(j0) + c] = gj[c];
     wave_sync();
     double pj[2];
-    tile_block_matvec(H, wv.vs, sh, 1, lane, w, c0, pj);
+    tile_block_matvec(H, sh.vs, sh, 1, lane, w, c0, pj);
 #pragma unroll
     for (int c = 0; c < 2; ++c) pj[c] = j0 + c < d ? -pj[c] : 0.0;
     double ddir = slot_dot<64, 2>(gj, pj);
@@ -276,7 +274,7 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
       ddir = slot_dot<64, 2>(gj, pj);
     }
 #pragma unroll
-    for (int c = 0; c < 2; ++c) wv.ps[j0 + c] = pj[c];
+    for (int c = 0; c < 2; ++c) sh.ps[j0 + c] = pj[c];
     wave_sync();
     // the stopping bound for the next test, read by one thread for the block
     // and published by the search's first barrier: the bound falls while the
@@ -286,9 +284,9 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
     // -- Armijo backtracking (Alg. 6) ---------------------------------------
     int taken;
     if (hi) {
-      taken = block_armijo<OBJ, double, kTDim>(sh, wv.xs, wv.ps, f, ddir, lsphase, &acc);
+      taken = block_armijo<OBJ, double, kTDim>(sh, sh.xs, sh.ps, f, ddir, lsphase, &acc);
     } else {
-      taken = block_armijo<OBJ, T, kTDim>(sh, wv.xs, wv.ps, f, ddir, lsphase, &acc);
+      taken = block_armijo<OBJ, T, kTDim>(sh, sh.xs, sh.ps, f, ddir, lsphase, &acc);
       if (taken < 0) {
         ls_trials += q.iter_ls;
         hi = true;  // escalate: FP32 cannot resolve this decrease
@@ -305,10 +303,10 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
     wave_sync();  // the wavefront has read xs in its trials
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      const double xnew = xj[c] + alpha * wv.ps[j0 + c];
+      const double xnew = xj[c] + alpha * sh.ps[j0 + c];
       sj[c] = j0 + c < d ? xnew - xj[c] : 0.0;
       xj[c] = j0 + c < d ? xnew : 0.0;
-      wv.xs[j0 + c] = xj[c];
+      sh.xs[j0 + c] = xj[c];
     }
   }
 }
