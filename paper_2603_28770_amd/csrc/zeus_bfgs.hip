@@ -161,8 +161,9 @@ hipError_t launch_prec(const Group &g, int64_t want, int cus) {
 }  // namespace
 
 // Tiling: lanes per start (2..64, a power of two >= dim: one group per start,
-// H in registers), kTileBlockDim (one block of four wavefronts per start, H in
-// their registers, dim <= 128), kHybridDim (one block of eight wavefronts per
+// H in registers), kTile3Dim (one block of three wavefronts per start, H in
+// their registers, dim <= 96; not for user objectives, which have a lane per
+// coordinate of 128), kTileBlockDim (four wavefronts, dim <= 128), kHybridDim (one block of eight wavefronts per
 // start, H in their registers and LDS, dim <= 208) or kWideLanes (one block
 // per start, H in device memory).
 // Every tiling computes the same pairwise trees, so results do not depend on
@@ -180,6 +181,7 @@ hipError_t launch_prec(const Group &g, int64_t want, int cus) {
 namespace {
 bool tiling_valid(int lanes, int dim) {
   if (lanes == kWideLanes) return dim <= kMaxDim;
+  if (lanes == kTile3Dim) return dim <= kTile3Dim;
   if (lanes == kTileBlockDim) return dim <= kTileBlockDim;
   if (lanes == kHybridDim) return dim <= kHybridDim;
   return lanes >= 2 && lanes <= kMaxNarrowDim && (lanes & (lanes - 1)) == 0 && lanes >= dim;
@@ -189,10 +191,13 @@ bool tiling_valid(int lanes, int dim) {
 int group_lanes(int objective, int precision, int dim) {
   if (const char *e = getenv("ZEUS_TILE_LANES")) {
     const int v = atoi(e);
-    if (v > 0 && tiling_valid(v, dim)) return v;
+    if (v > 0 && tiling_valid(v, dim) && !(v == kTile3Dim && objective == kUser)) return v;
   }
   if (dim > kMaxNarrowDim)
-    return dim <= kTileBlockDim ? kTileBlockDim : dim <= kHybridDim ? kHybridDim : kWideLanes;
+    return dim <= kTile3Dim && objective != kUser ? kTile3Dim
+           : dim <= kTileBlockDim              ? kTileBlockDim
+           : dim <= kHybridDim                 ? kHybridDim
+                                               : kWideLanes;
   for (const TileRule &r : kTileRules)
     if (r.objective == objective && r.precision == precision && dim >= r.dmin && dim <= r.dmax &&
         tiling_valid(r.lanes, dim))
@@ -222,9 +227,9 @@ hipError_t launch_bfgs(const Group &g) {
   }
   if (g.method == 1) return launch_lbfgs(g, cus);
   if (g.g_bfgs == kWideLanes) return launch_bfgs_wide(g, cus);
-  if (g.g_bfgs == kTileBlockDim || g.g_bfgs == kHybridDim) {
+  if (g.g_bfgs == kTile3Dim || g.g_bfgs == kTileBlockDim || g.g_bfgs == kHybridDim) {
     if (g.objective == kUser) return launch_user_bfgs(g, g.total_starts, cus);
-    return g.g_bfgs == kTileBlockDim ? launch_bfgs_tile(g, cus) : launch_bfgs_hybrid(g, cus);
+    return g.g_bfgs == kHybridDim ? launch_bfgs_hybrid(g, cus) : launch_bfgs_tile(g, cus);
   }
   if (g.g_bfgs > kMaxNarrowDim) return hipErrorInvalidValue;
   const int64_t starts_per_block = (int64_t)(kBfgsBlock / g.g_bfgs);

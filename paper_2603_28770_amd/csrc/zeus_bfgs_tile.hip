@@ -1,4 +1,5 @@
-// zeus_bfgs_tile.hip -- launches of the on-chip block kernel for 64 < d <= 128
+// zeus_bfgs_tile.hip -- launches of the on-chip block kernels for 64 < d <= 128:
+// three wavefronts per start up to 96, four above
 // (the kernel template is in zeus_bfgs_tile_kernels.h).
 #include "zeus_bfgs_tile_kernels.h"
 
@@ -6,11 +7,11 @@ namespace zeus {
 namespace {
 
 // The kernel is persistent: as many blocks as can be resident at once.
-template <int OBJ, class T>
-hipError_t launch_tile_t(const Group &g, int cus) {
+template <int OBJ, class T, int NB>
+hipError_t launch_tile_nb(const Group &g, int cus) {
   int per_cu = 0;
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      &per_cu, reinterpret_cast<const void *>(&bfgs_tile_kernel<OBJ, T>), kBlockLanes, 0);
+      &per_cu, reinterpret_cast<const void *>(&bfgs_tile_kernel<OBJ, T, NB>), 64 * kTWaves<NB>, 0);
   if (e != hipSuccess) return e;
   if (per_cu < 1) per_cu = 1;
   const int64_t cap = (int64_t)cus * per_cu;
@@ -19,9 +20,14 @@ hipError_t launch_tile_t(const Group &g, int cus) {
     return hipSuccess;
   }
   const int blocks = (int)(g.total_starts < cap ? g.total_starts : cap);
-  hipLaunchKernelGGL((bfgs_tile_kernel<OBJ, T>), dim3(blocks), dim3(kBlockLanes), 0, g.stream,
+  hipLaunchKernelGGL((bfgs_tile_kernel<OBJ, T, NB>), dim3(blocks), dim3(64 * kTWaves<NB>), 0, g.stream,
                      g.reqs, g.nreq, g.hdr, g.total_starts);
   return hipGetLastError();
+}
+
+template <int OBJ, class T>
+hipError_t launch_tile_t(const Group &g, int cus) {
+  return g.g_bfgs == kTile3Dim ? launch_tile_nb<OBJ, T, 6>(g, cus) : launch_tile_nb<OBJ, T, 8>(g, cus);
 }
 
 template <class T>

@@ -1,24 +1,30 @@
 // zeus_bfgs_tile_kernels.h -- the BFGS phase for 64 < d <= 128 with the
 // inverse Hessian on chip (Alg. 4 / Alg. 10 with the dual-number gradient of
-// Alg. 5 and the Armijo search of Alg. 6): one block of four wavefronts per
-// start.  Built into the library (zeus_bfgs_tile.hip) and into the run-time
-// program of a user objective.
+// Alg. 5 and the Armijo search of Alg. 6): one block of three (d <= 96) or
+// four wavefronts per start.  Built into the library (zeus_bfgs_tile.hip) and,
+// with four wavefronts, into the run-time program of a user objective.
 //
-//  * H is 128 x 128 (zero-padded past the dimension, ones on the padded
-//    diagonal) and split into four 64 x 64 quarters, one per wavefront:
-//    wavefront w holds rows 64 (w & 1) .. + 63 and columns 64 (w >> 1) .. + 63
-//    in its registers, in the 4 x 16 tiles of the narrow kernel's 64-lane
-//    groups (zeus_group.h Tile), so H never leaves the chip;
+//  * H is padded to 96 x 96 or 128 x 128 (zeros past the dimension, ones on
+//    the padded diagonal), all of it in the wavefronts' registers.  Three
+//    wavefronts hold two blocks of 16 columns each (ColumnTile); four hold a
+//    64 x 64 quarter each, in the 4 x 16 tiles of the narrow kernel's 64-lane
+//    groups (QuarterTile);
 //  * a row's product with a vector is a fused multiply-add chain over each
-//    block of 16 consecutive columns, the block sums added pairwise: inside a
-//    wavefront the four blocks of its quarter meet in two lane-swap levels,
-//    then the two quarters of a row are added through LDS, which is the
-//    pairwise tree over the eight blocks (the order of every other kernel);
-//    lane i of wavefronts w and w + 2 both end with row 64 (w & 1) + i;
+//    block of 16 consecutive columns, the block sums added pairwise: a
+//    wavefront's blocks of a row meet in lane swaps, its pieces of a row are
+//    added through LDS, which is the pairwise tree over the blocks (the order
+//    of every other kernel);
+//  * in the 128 columns of four wavefronts, d = 65 .. 96 did 1.8 times the work
+//    on H, with 224 registers and two blocks on a CU.  Three wavefronts of 96
+//    columns fit 168 registers and four blocks.  Rosenbrock, 8,192 starts:
+//    d = 96 35.0 -> 21.2 ms, d = 65 25.7 -> 15.4 ms (at two blocks still 32.5 and
+//    23.8); Styblinski-Tang d = 90 3.1 -> 1.9 ms; Ackley d = 70 1.77 -> 1.55 ms,
+//    with 67 registers spilled.  Columns split this way among four wavefronts
+//    need four pieces per row instead of two: d = 128 86.0 ms against 83.1;
 //  * every wavefront keeps all coordinates (lane l the coordinates 2 l and
 //    2 l + 1) and forms value, gradient and sums for itself, so an iteration
-//    has three barriers: one after each product's quarters (u = H y and
-//    H_new g) and one per line-search round (four trials, one per wavefront).
+//    has three barriers: one after each product's pieces (u = H y and
+//    H_new g) and one per line-search round (a trial per wavefront).
 //    The vectors the lanes exchange are shared in LDS: all wavefronts write
 //    the same values, and a vector is written again only after a barrier that
 //    follows its last reader (a copy per wavefront cost a user objective, which
@@ -42,56 +48,164 @@
 namespace zeus {
 namespace {
 
-constexpr int kTDim = kTileBlockDim;            // rows and columns of the padded H
-constexpr int kQuarter = 64;                    // rows and columns of a wavefront's part
+constexpr int kTDim = kTileBlockDim;            // coordinate slots (two per lane)
 constexpr int kTVec = tile_vec_len(kTDim);      // doubles of a padded operand vector
-static_assert(kTDim == 2 * kQuarter, "four wavefronts hold two by two quarters");
+template <int NB>
+constexpr int kTWaves = NB / 2;                 // wavefronts per start
 
+template <int NB>
 struct TileShm {
+  static constexpr int NW = kTWaves<NB>;
   double xs[kTDim];  // iterate under evaluation (x, then x_new), zero past d
   double ps[kTDim];  // search direction
   double vs[kTVec];  // y, then g: operand of u = H y and p = -H g, padded layout
   double ss[kTVec];  // s = x_new - x, padded layout
   double us[kTVec];  // u = H y, padded layout
-  double part[2][kBlockWaves][kQuarter];  // each wavefront's products over its quarter (u, H g)
-  double gx[kTDim];                       // the gradient, lane by lane (whole-form objectives)
-  double red[1][1][kBlockWaves];          // (its extent is the number of wavefronts)
-  double tsum[2 * kBlockWaves][kMaxSums];   // [phase * waves + wave][sum] line-search trials' term sums
+  double part[2][3][kTDim];   // [product: u, H g][piece][row]
+  double gx[kTDim];           // the gradient, lane by lane (whole-form objectives)
+  double red[1][1][NW];       // (its extent is the number of wavefronts)
+  double tsum[2 * NW][kMaxSums];   // [phase * waves + wave][sum] line-search trials' term sums
   double al[kTabTrials];
-  int pass[2][kBlockWaves];            // [phase][wave] line-search outcome
-  StartCounts cnt;                     // update skips and direction resets (thread 0)
+  int pass[2][NW];                 // [phase][wave] line-search outcome
+  StartCounts cnt;                 // update skips and direction resets (thread 0)
   unsigned long long got;
-  int bound;                           // early-stop bound
+  int bound;                       // early-stop bound
   ReqHot q;
 };
 
-// Row products of H with the vector whose entries this wavefront left in v
-// (padded layout): rows 2 lane and 2 lane + 1 in r.  Every wavefront forms its
-// quarter's products; after the barrier each adds the two quarters of every
-// row for itself.  The two products of an iteration use a buffer each, so a
-// buffer is written again only after the barrier of the other.
-__device__ __forceinline__ void tile_block_matvec(const Tile<64> &H, const double *v, TileShm &sh,
-                                                  int buf, int lane, int w, int c0, double (&r)[2]) {
-  sh.part[buf][w][lane] = H.matvec_bcast(v[vpos<kTDim>(c0 + lane)]);
-  __syncthreads();
-  const int hf = lane >> 5, i = (2 * lane) & 63;  // rows 2 lane, 2 lane + 1: half hf, place i, i + 1
+// The columns of one of three wavefronts: its 16-lane rows hold its two column
+// blocks for the upper and the lower 48 rows.  Lane l holds, for t < 3, row
+// 48 (l / 32) + 16 t + l mod 16 at the 16 columns of block 2 w + (l / 16) mod 2.
+struct ColumnTile {
+  static constexpr int R = 3;
+  double h[16 * R];
+  __device__ __forceinline__ static int row(int lane, int t) {
+    return 16 * R * (lane >> 5) + 16 * t + (lane & 15);
+  }
+  __device__ __forceinline__ static int col(int lane, int w) { return 16 * (2 * w + ((lane >> 4) & 1)); }
+
+  __device__ __forceinline__ void identity(int lane, int w) {
+    lane = Tile<64>::opaque(lane);
 #pragma unroll
-  for (int c = 0; c < 2; ++c) r[c] = sh.part[buf][hf][i + c] + sh.part[buf][hf + 2][i + c];
+    for (int t = 0; t < R; ++t)
+#pragma unroll
+      for (int k = 0; k < 16; ++k) h[16 * t + k] = row(lane, t) == col(lane, w) + k ? 1.0 : 0.0;
+  }
+  __device__ __forceinline__ void restore_padding(int lane, int w, int d) {
+    lane = Tile<64>::opaque(lane);
+#pragma unroll
+    for (int t = 0; t < R; ++t)
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const int r = row(lane, t), c = col(lane, w) + k;
+        if (r >= d || c >= d) h[16 * t + k] = r == c ? 1.0 : 0.0;
+      }
+  }
+  // The rows' sums over the wavefront's two blocks, piece w of the product with
+  // the padded vector v.
+  __device__ __forceinline__ void matvec(const double *v, int lane, int w, double (*part)[kTDim]) const {
+    const double vc = v[vpos<kTDim>(col(lane, w)) + (lane & 15)];
+    double *out = part[w];
+    double p[R];
+#pragma unroll
+    for (int t = 0; t < R; ++t) p[t] = 0.0;
+    static_for<0, 16>([&](auto kk) {
+      constexpr int k = decltype(kk)::value;
+      fmac_bcast<k>(p[0], p[1], p[2], vc, h[k], h[16 + k], h[32 + k]);
+    });
+    // one swap leaves row t's sum in the first block's lanes, row t + 1's in
+    // the second's
+    const int r = row(lane, 0), up = lane & 16;
+    out[r + up] = half_pair_sum<16>(p[0], p[1]);
+    out[r + 32] = half_pair_sum<16>(p[2], p[2]);  // the same value in both
+  }
+  // H <- H - rho (s u' + u s') + beta s s', as Tile::rank2_bcast; false when a
+  // coefficient is not finite.
+  __device__ __forceinline__ bool rank2(double rho, double beta, const double *us, const double *ss,
+                                        int lane, int w) {
+    double a[R], e[R];
+    bool fin = true;
+#pragma unroll
+    for (int t = 0; t < R; ++t) {
+      const int r = vpos<kTDim>(row(lane, t));
+      const double sr = ss[r], ur = us[r];
+      a[t] = -rho * sr;
+      e[t] = beta * sr - rho * ur;
+      fin = fin && __builtin_isfinite(a[t]) && __builtin_isfinite(e[t]);
+    }
+    const int c = vpos<kTDim>(col(lane, w)) + (lane & 15);
+    const double uc = us[c], sc = ss[c];
+    static_for<0, 16>([&](auto kk) {
+      constexpr int k = decltype(kk)::value;
+      upd_bcast<k>(h[k], h[16 + k], h[32 + k], uc, sc, a, e);
+    });
+    return fin;
+  }
+};
+
+// The 64 x 64 quarters of four wavefronts: rows 64 (w & 1) .., columns
+// 64 (w >> 1) ...
+struct QuarterTile {
+  Tile<64> t;
+  __device__ __forceinline__ void identity(int lane, int w) {
+    t.identity_at(lane, 64 * (w & 1), 64 * (w >> 1));
+  }
+  __device__ __forceinline__ void restore_padding(int lane, int w, int d) {
+    t.restore_padding_at(lane, d, 64 * (w & 1), 64 * (w >> 1));
+  }
+  __device__ __forceinline__ void matvec(const double *v, int lane, int w, double (*part)[kTDim]) const {
+    part[w >> 1][64 * (w & 1) + lane] = t.matvec_bcast(v[vpos<kTDim>(64 * (w >> 1) + lane)]);
+  }
+  __device__ __forceinline__ bool rank2(double rho, double beta, const double *us, const double *ss,
+                                        int lane, int w) {
+    const int r0 = vpos<kTDim>(64 * (w & 1)), c = vpos<kTDim>(64 * (w >> 1) + lane);
+    return t.rank2_bcast(rho, beta, us + r0, ss + r0, us[c], ss[c], lane, 0.0, 0.0);
+  }
+};
+template <int NB>
+struct TileOf {
+  using type = QuarterTile;
+};
+template <>
+struct TileOf<6> {
+  using type = ColumnTile;
+};
+
+// Row products of H with the padded vector v: rows 2 lane and 2 lane + 1 in r.
+// Every wavefront forms its columns' part; after the barrier each adds the
+// pieces of every row for itself.  The two products of an iteration use a
+// buffer each, so a buffer is written again only after the barrier of the
+// other.
+template <int NB>
+__device__ __forceinline__ void tile_block_matvec(const typename TileOf<NB>::type &H, const double *v,
+                                                  TileShm<NB> &sh, int buf, int lane, int w,
+                                                  double (&r)[2]) {
+  H.matvec(v, lane, w, sh.part[buf]);
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    const int i = 2 * lane + c;
+    r[c] = sh.part[buf][0][i] + sh.part[buf][1][i];
+    if constexpr (NB == 6) r[c] = r[c] + sh.part[buf][2][i];
+  }
 }
 
+// Waves per SIMD the register allocation must allow.
+template <int NB>
+constexpr int kTileWavesPerSimd = NB == 6 ? 3 : 2;
+
 // See the narrow kernel for the mixed-precision rules (T = float).
-template <int OBJ, class T>
-__global__ __launch_bounds__(kBlockLanes) __attribute__((amdgpu_waves_per_eu(2)))
+template <int OBJ, class T, int NB>
+__global__ __launch_bounds__(64 * kTWaves<NB>) __attribute__((amdgpu_waves_per_eu(kTileWavesPerSimd<NB>)))
 void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total) {
   constexpr bool kMixed = sizeof(T) != sizeof(double);
   constexpr bool kWhole = whole_form<Elem<OBJ>>::value;
-  __shared__ TileShm sh;
+  __shared__ TileShm<NB> sh;
   const GroupLanes<64> L;
   const int j = threadIdx.x;
   const int lane = j & 63, w = __builtin_amdgcn_readfirstlane(j >> 6);
-  const int r0 = kQuarter * (w & 1), c0 = kQuarter * (w >> 1);  // this wavefront's quarter
   const int j0 = 2 * lane;                                      // the lane's coordinates j0, j0 + 1
-  Tile<64> H;
+  typename TileOf<NB>::type H;
   int lsphase = 0;
   int acc = -1;  // slot of sh.tsum with the accepted trial's term sums (block_armijo), or -1
   bool first = true, fresh = false, hi = !kMixed;
@@ -126,7 +240,7 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
         sh.cnt = StartCounts{0, 0};
         sh.bound = es_bound(sh.q);
       }
-      fill_step_lengths(sh.al, rq.shrink, j, kBlockLanes);
+      fill_step_lengths(sh.al, rq.shrink, j, 64 * kTWaves<NB>);
 #pragma unroll
       for (int c = 0; c < 2; ++c) {
         xj[c] = j0 + c < d0 ? rq.ws.x[idx * d0 + j0 + c] : 0.0;  // x <- swarm[i]
@@ -146,6 +260,7 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
     // -- value and gradient at xs, on every wavefront ---------------------------
     double gn[2], fn;
     if constexpr (kWhole) {
+      static_assert(!kWhole || 64 * kTWaves<NB> >= kTDim, "a lane per coordinate");
       // user code of unknown cost: a pass per coordinate, once in the block
       double g1[1];
       if (hi)
@@ -182,7 +297,7 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
         for (int c = 0; c < 2; ++c) sh.vs[vpos<kTDim>(j0) + c] = yj[c];
         wave_sync();
         double uj[2];
-        tile_block_matvec(H, sh.vs, sh, 0, lane, w, c0, uj);
+        tile_block_matvec<NB>(H, sh.vs, sh, 0, lane, w, uj);
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
           uj[c] = j0 + c < d ? uj[c] : 0.0;
@@ -194,10 +309,7 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
         wave_sync();
         // H+ = H - rho (s u' + u s') + beta s s'   (u = H y); inf * 0 would
         // have reached the padding when a coefficient is not finite
-        if (!H.rank2_bcast(rho, beta, sh.us + vpos<kTDim>(r0), sh.ss + vpos<kTDim>(r0),
-                           sh.us[vpos<kTDim>(c0 + lane)], sh.ss[vpos<kTDim>(c0 + lane)], lane, 0.0,
-                           0.0))
-          H.restore_padding_at(lane, d, r0, c0);
+        if (!H.rank2(rho, beta, sh.us, sh.ss, lane, w)) H.restore_padding(lane, w, d);
       } else if (j == 0) {
         ++sh.cnt.skips;
       }
@@ -256,19 +368,19 @@ void bfgs_tile_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total
     // H is the identity until the first update (k = 0).  Setting it here
     // rather than at the claim keeps the old tile's registers from being
     // live beside the new one's (the claim path rejoins the loop with H).
-    if (k == 0) H.identity_at(lane, r0, c0);
+    if (k == 0) H.identity(lane, w);
     wave_sync();  // the product of y has read vs
 #pragma unroll
     for (int c = 0; c < 2; ++c) sh.vs[vpos<kTDim>(j0) + c] = gj[c];
     wave_sync();
     double pj[2];
-    tile_block_matvec(H, sh.vs, sh, 1, lane, w, c0, pj);
+    tile_block_matvec<NB>(H, sh.vs, sh, 1, lane, w, pj);
 #pragma unroll
     for (int c = 0; c < 2; ++c) pj[c] = j0 + c < d ? -pj[c] : 0.0;
     double ddir = slot_dot<64, 2>(gj, pj);
     if (!(ddir < 0.0)) {
       if (j == 0) ++sh.cnt.resets;
-      H.identity_at(lane, r0, c0);
+      H.identity(lane, w);
 #pragma unroll
       for (int c = 0; c < 2; ++c) pj[c] = j0 + c < d ? -gj[c] : 0.0;
       ddir = slot_dot<64, 2>(gj, pj);

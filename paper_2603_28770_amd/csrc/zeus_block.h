@@ -13,7 +13,7 @@ constexpr int kBlockLanes = kWideLanes;     // lanes (threads) per start (four w
 constexpr int kBlockWaves = kBlockLanes / 64;  // wavefronts per start == trials per round
 static_assert(kBlockWaves == 4, "the device-memory and on-chip blocks have four wavefronts");
 
-// The wavefronts of the block (4 or 8), from the LDS struct's sum slots.
+// The wavefronts of the block (3, 4 or 8), from the LDS struct's sum slots.
 template <class Shm>
 constexpr int shm_waves() {
   return (int)(sizeof(Shm::red[0][0]) / sizeof(double));

@@ -196,6 +196,17 @@ __device__ __forceinline__ void fmac_bcast(double &a0, double &a1, double v, dou
       : "v"(v), "v"(h0), "v"(h1), "n"(K));
 }
 template <int K>
+__device__ __forceinline__ void fmac_bcast(double &a0, double &a1, double &a2, double v, double h0,
+                                           double h1, double h2) {
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %3, %4 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %3, %5 row_newbcast:%7 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %3, %6 row_newbcast:%7 row_mask:0xf bank_mask:0xf"
+      : "+v"(a0), "+v"(a1), "+v"(a2)
+      : "v"(v), "v"(h0), "v"(h1), "v"(h2), "n"(K));
+}
+template <int K>
 __device__ __forceinline__ void fmac_bcast(double &a0, double &a1, double &a2, double &a3, double v,
                                            double h0, double h1, double h2, double h3) {
   asm volatile(
@@ -228,6 +239,20 @@ __device__ __forceinline__ void upd_bcast(double &x0, double &x1, double u, doub
       "v_fmac_f64_dpp %1, %3, %7 row_newbcast:%8 row_mask:0xf bank_mask:0xf"
       : "+v"(x0), "+v"(x1)
       : "v"(u), "v"(s), "v"(a0), "v"(a1), "v"(e0), "v"(e1), "n"(K));
+}
+template <int K>
+__device__ __forceinline__ void upd_bcast(double &x0, double &x1, double &x2, double u, double s,
+                                          const double (&a)[3], const double (&e)[3]) {
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %3, %5 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %3, %6 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %3, %7 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %4, %8 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %4, %9 row_newbcast:%11 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %4, %10 row_newbcast:%11 row_mask:0xf bank_mask:0xf"
+      : "+v"(x0), "+v"(x1), "+v"(x2)
+      : "v"(u), "v"(s), "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(e[0]), "v"(e[1]), "v"(e[2]), "n"(K));
 }
 template <int K>
 __device__ __forceinline__ void upd_bcast(double &x0, double &x1, double &x2, double &x3, double u,

@@ -95,7 +95,7 @@ int user_compile(const char *arch, const char *source, UserKernels *out, std::st
     for (int l = 2; l <= 6; ++l)
       bfgs_expr.push_back("&zeus::bfgs_kernel<7, " + std::to_string(1 << l) + ", " + t + ">");
     for (int l = 2; l <= 8; ++l) lbfgs_expr.push_back("&zeus::lbfgs_kernel<7, " + split(l) + ", " + t + ">");
-    block_expr.push_back(std::string("&zeus::bfgs_tile_kernel<7, ") + t + ">");
+    block_expr.push_back(std::string("&zeus::bfgs_tile_kernel<7, ") + t + ", 8>");
     block_expr.push_back(std::string("&zeus::bfgs_hybrid_kernel<7, ") + t + ">");
   }
   for (const auto *v : {&pso_expr, &bfgs_expr, &lbfgs_expr, &block_expr})

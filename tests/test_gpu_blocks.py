@@ -33,8 +33,10 @@ def _same(a, b):
     return np.array_equal(a, b, equal_nan=a.dtype.kind == "f")
 
 
-# (lanes forced, dimensions): four wavefronts, eight with H on chip, eight with a slot
-CASES = ([(128, d) for d in (65, 66, 80, 81, 127, 128)]
+# (lanes forced, dimensions): three and four wavefronts, eight with H on chip, eight
+# with a slot
+CASES = ([(96, d) for d in (33, 48, 49, 64, 65, 80, 81, 95, 96)]
+         + [(128, d) for d in (65, 66, 80, 81, 97, 127, 128)]
          + [(208, d) for d in (100, 129, 144, 145, 160, 176, 177, 192, 193, 207, 208)]
          + [(256, d) for d in (65, 128, 129, 160, 192, 193, 209, 224, 225, 240, 241, 255, 256)])
 
@@ -52,7 +54,7 @@ def test_block_edges(Z, ctx, oracle_mod, monkeypatch, lanes, d, objective):
         assert _same(g[k], o[k]), k
 
 
-@pytest.mark.parametrize("lanes,d", [(128, 100), (208, 150), (208, 200), (256, 230)])
+@pytest.mark.parametrize("lanes,d", [(96, 90), (128, 100), (208, 150), (208, 200), (256, 230)])
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 def test_blocks_share_a_launch(Z, ctx, monkeypatch, lanes, d, precision):
     # two dimensions and an early stop in one launch: a block goes from one
@@ -70,7 +72,7 @@ def test_blocks_share_a_launch(Z, ctx, monkeypatch, lanes, d, precision):
             assert _same(g[k], alone[k]), (p["dim"], k)
 
 
-@pytest.mark.parametrize("lanes,d", [(128, 90), (208, 170), (208, 205), (256, 211)])
+@pytest.mark.parametrize("lanes,d", [(96, 70), (128, 90), (208, 170), (208, 205), (256, 211)])
 def test_blocks_diverging_starts(Z, ctx, oracle_mod, monkeypatch, lanes, d):
     # one trial per search: alpha = 1/2 is taken unverified and the starts run
     # off until a value is not finite, through updates whose coefficients are
