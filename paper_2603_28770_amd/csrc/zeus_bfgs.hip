@@ -112,12 +112,12 @@ __global__ __launch_bounds__(64) void es_finish_kernel(const ReqDev *reqs, int n
 
 // The kernel is persistent: it gets as many blocks as can be resident at once
 // (more would only start once the work counter is spent).
-template <int OBJ, int G, class T>
+template <int OBJ, int G, class T, bool kCut = false>
 hipError_t launch_g(const Group &g, int64_t want, int cus) {
-  const size_t lds = sizeof(double) * (size_t)group_stride(G) * (kBfgsBlock / G);
+  const size_t lds = sizeof(double) * (size_t)group_stride(G, kCut) * (kBfgsBlock / G);
   int per_cu = 0;
   hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      &per_cu, reinterpret_cast<const void *>(&bfgs_kernel<OBJ, G, T>), kBfgsBlock, lds);
+      &per_cu, reinterpret_cast<const void *>(&bfgs_kernel<OBJ, G, T, kCut>), kBfgsBlock, lds);
   if (e != hipSuccess) return e;
   if (per_cu < 1) per_cu = 1;
   const int64_t cap = (int64_t)cus * per_cu;
@@ -126,9 +126,17 @@ hipError_t launch_g(const Group &g, int64_t want, int cus) {
     return hipSuccess;
   }
   const int blocks = (int)(want < cap ? want : cap);
-  hipLaunchKernelGGL((bfgs_kernel<OBJ, G, T>), dim3(blocks), dim3(kBfgsBlock), lds, g.stream,
+  hipLaunchKernelGGL((bfgs_kernel<OBJ, G, T, kCut>), dim3(blocks), dim3(kBfgsBlock), lds, g.stream,
                      g.reqs, g.nreq, g.hdr, g.total_starts);
   return hipGetLastError();
+}
+
+// Objectives with a cut-tile kernel.  With the transcendental ones the 168
+// VGPRs of three waves do not hold the terms beside H (80 to 180 spilled: Ackley
+// d = 50, 131,072 starts, 6.0 -> 12.0 ms), and at two waves the cut tile gains
+// nothing (6.0 -> 6.1 ms).  User objectives are compiled for powers of two.
+constexpr bool cut_objective(int o) {
+  return o == kRosenbrock || o == kStyblinskiTang || o == kSphere || o == kQuartic;
 }
 
 template <int OBJ, class T>
@@ -139,6 +147,17 @@ hipError_t launch_obj(const Group &g, int64_t want, int cus) {
     case 8: return launch_g<OBJ, 8, T>(g, want, cus);
     case 16: return launch_g<OBJ, 16, T>(g, want, cus);
     case 32: return launch_g<OBJ, 32, T>(g, want, cus);
+    // The cut tile's wavefront takes a fifth longer over an iteration by itself
+    // but three fit on a SIMD: it gains from the first start that the other
+    // kernel's two wavefronts per SIMD leave over (2,048 on 256 compute units;
+    // Rosenbrock d = 50, cut against not: 1.30 / 1.13 ms at 1,000 starts, 1.55 /
+    // 1.48 at 2,000, 1.70 / 1.92 at 2,500, 4.1 / 4.4 at 8,192, 48.2 / 57.1 at
+    // 131,072).
+    case kCutDim:
+      if constexpr (cut_objective(OBJ))
+        if (g.resident || g.total_starts > 8 * (int64_t)cus)
+          return launch_g<OBJ, 64, T, true>(g, want, cus);
+      return launch_g<OBJ, 64, T>(g, want, cus);
     case 64: return launch_g<OBJ, 64, T>(g, want, cus);
     default: return hipErrorInvalidValue;
   }
@@ -160,12 +179,13 @@ hipError_t launch_prec(const Group &g, int64_t want, int cus) {
 
 }  // namespace
 
-// Tiling: lanes per start (2..64, a power of two >= dim: one group per start,
-// H in registers), kTile3Dim (one block of three wavefronts per start, H in
-// their registers, dim <= 96; not for user objectives, which have a lane per
-// coordinate of 128), kTileBlockDim (four wavefronts, dim <= 128), kHybridDim (one block of eight wavefronts per
-// start, H in their registers and LDS, dim <= 208) or kWideLanes (one block
-// per start, H in device memory).
+// Tiling: lanes per start (2..64, a power of two >= dim: one group per start, H
+// in registers), kCutDim (64 lanes with the cut tile, dim <= 52), kTile3Dim
+// (one block of three wavefronts per start, H in their registers, dim <= 96;
+// not for user objectives, which have a lane per coordinate of 128),
+// kTileBlockDim (four wavefronts, dim <= 128), kHybridDim (one block of eight
+// wavefronts per start, H in their registers and LDS, dim <= 208) or kWideLanes
+// (one block per start, H in device memory).
 // Every tiling computes the same pairwise trees, so results do not depend on
 // it; only speed does.  The rules come from the autotuner's table; a start
 // no rule covers gets the smallest power of two >= max(dim, 4), or above 64
@@ -179,9 +199,10 @@ hipError_t launch_prec(const Group &g, int64_t want, int cus) {
 #include "zeus_tiling.inc"
 
 namespace {
-bool tiling_valid(int lanes, int dim) {
+bool tiling_valid(int objective, int lanes, int dim) {
   if (lanes == kWideLanes) return dim <= kMaxDim;
-  if (lanes == kTile3Dim) return dim <= kTile3Dim;
+  if (lanes == kCutDim) return dim <= kCutDim && cut_objective(objective);
+  if (lanes == kTile3Dim) return dim <= kTile3Dim && objective != kUser;
   if (lanes == kTileBlockDim) return dim <= kTileBlockDim;
   if (lanes == kHybridDim) return dim <= kHybridDim;
   return lanes >= 2 && lanes <= kMaxNarrowDim && (lanes & (lanes - 1)) == 0 && lanes >= dim;
@@ -191,7 +212,7 @@ bool tiling_valid(int lanes, int dim) {
 int group_lanes(int objective, int precision, int dim) {
   if (const char *e = getenv("ZEUS_TILE_LANES")) {
     const int v = atoi(e);
-    if (v > 0 && tiling_valid(v, dim) && !(v == kTile3Dim && objective == kUser)) return v;
+    if (v > 0 && tiling_valid(objective, v, dim)) return v;
   }
   if (dim > kMaxNarrowDim)
     return dim <= kTile3Dim && objective != kUser ? kTile3Dim
@@ -200,8 +221,8 @@ int group_lanes(int objective, int precision, int dim) {
                                                : kWideLanes;
   for (const TileRule &r : kTileRules)
     if (r.objective == objective && r.precision == precision && dim >= r.dmin && dim <= r.dmax &&
-        tiling_valid(r.lanes, dim))
-      return r.lanes;
+        tiling_valid(objective, r.lanes, dim))
+      return r.lanes == 64 && tiling_valid(objective, kCutDim, dim) ? kCutDim : r.lanes;
   if (objective == kUser && dim <= 8) return 32;
   int g = 4;
   while (g < dim) g <<= 1;
@@ -232,7 +253,7 @@ hipError_t launch_bfgs(const Group &g) {
     return g.g_bfgs == kHybridDim ? launch_bfgs_hybrid(g, cus) : launch_bfgs_tile(g, cus);
   }
   if (g.g_bfgs > kMaxNarrowDim) return hipErrorInvalidValue;
-  const int64_t starts_per_block = (int64_t)(kBfgsBlock / g.g_bfgs);
+  const int64_t starts_per_block = kBfgsBlock / (g.g_bfgs == kCutDim ? 64 : g.g_bfgs);
   const int64_t want = (g.total_starts + starts_per_block - 1) / starts_per_block;
   if (g.objective == kUser) return launch_user_bfgs(g, want, cus);
   if (g.precision == ZEUS_MIXED) return launch_prec<float>(g, want, cus);

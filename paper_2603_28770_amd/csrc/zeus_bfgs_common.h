@@ -82,7 +82,9 @@ __device__ __forceinline__ int request_of(const ReqDev *reqs, int nreq, int64_t 
 // written but without the square root when gg >= 4 bound^2: there the root
 // is at least twice the bound up to a few roundings, so the test fails.
 __device__ __forceinline__ bool norm_below(double gg, double bound) {
-  if (!(gg < (4.0 * bound) * bound)) return false;
+  const bool near = gg < (4.0 * bound) * bound;
+  if (__ballot(near) == 0ull) return false;  // (per lane, the root would be taken every time)
+  if (!near) return false;
   return sqrt(gg) < bound;
 }
 
@@ -283,6 +285,13 @@ __device__ __forceinline__ double trial_value(const double *xs, const double *ps
   return (double)E::template outer<U>(d, sums);
 }
 
+// v of one lane of the wave (the same number on every lane).
+__device__ __forceinline__ double read_lane(double v, int lane) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  return __builtin_bit_cast(double, ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(b >> 32), lane) << 32) |
+                                        (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane));
+}
+
 // The Armijo searches (Alg. 6) of a wave's groups, the objective evaluated in
 // number type U.  Every lane of the wave must call it; need (the same on all
 // lanes of a group) says which groups search, the others lend their lanes;
@@ -306,11 +315,12 @@ __device__ __forceinline__ double trial_value(const double *xs, const double *ps
 // was slower (Ackley d = 2, 4,096 starts 9.4 ms against 7.6), and so was
 // sharing after two rounds (Rastrigin d = 6 4.3 ms).
 //
-// The group sees what is written to acc after its next wave_sync.
+// The group sees what is written to acc after its next wave_sync.  kept, where a
+// wave has one group, receives the accepted trial's term sums on every lane.
 template <int OBJ, int G, int SLOTS, int TP, class U>
 __device__ __forceinline__ int wave_search(const GroupLanes<G> &L, const HotRegs<G> &hot, bool need,
                                            double f, double ddir, double *wave_lds,
-                                           const SearchLayout &lay) {
+                                           const SearchLayout &lay, double *kept = nullptr) {
   using E = Elem<OBJ>;
   constexpr int R = G / TP, S = 64 / G;
   static_assert(TP >= 1 && TP <= G && G % TP == 0 && SLOTS % TP == 0, "whole trials per group");
@@ -356,6 +366,11 @@ __device__ __forceinline__ int wave_search(const GroupLanes<G> &L, const HotRegs
 #pragma unroll
             for (int kk = 0; kk < E::K; ++kk)
               wave_lds[L.grp * lay.stride + lay.acc + kk] = (double)sums[kk];
+        if constexpr (S == 1 && !whole_form<E>::value) {
+          if (kept)
+#pragma unroll
+            for (int kk = 0; kk < E::K; ++kk) kept[kk] = read_lane((double)sums[kk], first * TP);
+        }
         if constexpr (S == 1) return taken;  // the wave's only group (mine is a scalar there)
       }
       base += R;

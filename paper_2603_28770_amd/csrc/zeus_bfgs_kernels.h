@@ -42,13 +42,26 @@ struct GroupShm {
   ReqHot *q;   // the start's request
 };
 
-// Doubles per group slice (the last one is the searches' scratch).
-__device__ __host__ __forceinline__ constexpr int group_stride(int G) {
-  return 2 * G + 3 * tile_vec_len(G) + kTabTrials + kHotDoubles + 3;
+// Doubles per group slice (the last one is the searches' scratch; with the cut
+// tile its products' scratch follows).
+__device__ __host__ __forceinline__ constexpr int group_stride(int G, bool cut = false) {
+  return 2 * G + 3 * tile_vec_len(G) + kTabTrials + kHotDoubles + 3 + (cut ? kCutScratch : 0);
 }
-__device__ __host__ __forceinline__ constexpr SearchLayout group_search_layout(int G) {
+__device__ __host__ __forceinline__ constexpr SearchLayout group_search_layout(int G, bool cut) {
   const int al = 2 * G + 3 * tile_vec_len(G), q = al + kTabTrials, fd = q + kHotDoubles;
-  return SearchLayout{group_stride(G), 0, G, al, q, fd, fd + 2, -1};
+  return SearchLayout{group_stride(G, cut), 0, G, al, q, fd, fd + 2, -1};
+}
+
+// A value that is the same on every lane of the wave, kept in scalar registers.
+template <class V>
+__device__ __forceinline__ V uniform(V v) {
+  if constexpr (sizeof(V) == 4) {
+    return __builtin_bit_cast(V, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+  } else {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    return __builtin_bit_cast(V, ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(b >> 32)) << 32) |
+                                     (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b));
+  }
 }
 
 // T = double: every step in FP64.
@@ -71,16 +84,21 @@ __device__ __host__ __forceinline__ constexpr SearchLayout group_search_layout(i
 // three waves help Rastrigin's 16-lane kernel the same way.  The polynomial
 // objectives' kernels lie a few registers above the next occupancy at 8 to 32
 // lanes (Rosenbrock d = 20 in mixed precision, 16,384 starts: 1.88 ms at two
-// waves, 1.57 at three; d = 10, 65,536 starts: 1.21 at three, 1.14 at four).  Other kernels reach their occupancy without the request, and
+// waves, 1.57 at three; d = 10, 65,536 starts: 1.21 at three, 1.14 at four).  The
+// cut tile exists for its third wave (VALU active 80 -> 85 % of the time at 7 %
+// fewer instructions: Rosenbrock d = 50, 131,072 starts, 57.1 -> 48.2 ms), for
+// which the kernel keeps x, g, p and s in LDS between their uses and the start's
+// counters in scalar registers.  Other kernels reach their occupancy without the request, and
 // user code is of unknown size.
-template <int OBJ, int G>
-constexpr int kBfgsWaves = G == 64 ? 2
+template <int OBJ, int G, bool kCut = false>
+constexpr int kBfgsWaves = kCut ? 3
+                           : G == 64 ? 2
                            : OBJ == kUser || OBJ == kAckley ? 1
                            : OBJ == kRastrigin ? (G == 16 ? 3 : 1)
                            : G == 32 ? 3 : G == 8 || G == 16 ? 4 : 1;
 
-template <int OBJ, int G, class T>
-__global__ __launch_bounds__(kBfgsBlock) __attribute__((amdgpu_waves_per_eu(kBfgsWaves<OBJ, G>)))
+template <int OBJ, int G, class T, bool kCut = false>
+__global__ __launch_bounds__(kBfgsBlock) __attribute__((amdgpu_waves_per_eu(kBfgsWaves<OBJ, G, kCut>)))
 void bfgs_kernel(const ReqDev *reqs, int nreq,
                                                           BatchDev *hdr, int64_t total) {
   using E = Elem<OBJ>;
@@ -91,7 +109,7 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
   const int j = L.j;
   GroupShm sh;
   {
-    double *base = smem + (size_t)((threadIdx.x >> 6) * S + L.grp) * group_stride(G);
+    double *base = smem + (size_t)((threadIdx.x >> 6) * S + L.grp) * group_stride(G, kCut);
     sh.xs = base;
     sh.ps = base + G;
     constexpr int VL = tile_vec_len(G);
@@ -101,12 +119,15 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
     sh.al = sh.us + VL;
     sh.q = reinterpret_cast<ReqHot *>(sh.al + kTabTrials);
   }
-  double *wave_lds = smem + (size_t)((threadIdx.x >> 6) * S) * group_stride(G);
-  constexpr SearchLayout lay = group_search_layout(G);
+  double *wave_lds = smem + (size_t)((threadIdx.x >> 6) * S) * group_stride(G, kCut);
+  constexpr SearchLayout lay = group_search_layout(G, kCut);
+  double *scr = wave_lds + group_stride(G);  // the cut tile's (one group per wave)
   constexpr int TP = kTrialLanes<OBJ, G>;
 
   bool own = false;
-  Tile<G> H;  // this lane's tile of the inverse Hessian (identity in the padding)
+  const int jv = kCut ? j : vpos<G>(j);
+  typename NarrowTile<G, kCut>::type H;  // this lane's tile of the inverse Hessian (identity in the padding)
+  if constexpr (kCut) H.place(sh.vs, scr, j);
   double xj = 0.0, gj = 0.0, pj = 0.0, sj = 0.0, f = 0.0;
   int64_t idx = -1;
   int k = 0, ls_trials = 0;
@@ -117,6 +138,9 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
   int claims = 0;  // starts claimed after the first (second early-stop pass)
   int cur_ri = -1;  // the request whose scalars and step lengths the group's LDS holds
   HotRegs<G> hot{};
+  // (one group per wave) the term sums of the trial that produced xs, when one did
+  double known[E::K] = {};
+  bool have = false;
 
   for (;;) {
     // -- claim a start when idle ------------------------------------------
@@ -161,6 +185,7 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
       xj = own ? rq.ws.x[idx * d0 + j] : 0.0;  // x <- swarm[i]
       sh.xs[j] = xj;
       H.identity(j);  // H <- I
+      if constexpr (kCut) sh.vs[jv] = sh.ss[jv] = 0.0;
       cnt = StartCounts{0, 0};
       k = 0;
       ls_trials = 0;
@@ -171,6 +196,15 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
     wave_sync();
     const ReqHot &q = *sh.q;
     const int d = hot.d;
+    if constexpr (kCut) {
+      k = uniform(k);
+      ls_trials = uniform(ls_trials);
+      cnt.skips = uniform(cnt.skips);
+      cnt.resets = uniform(cnt.resets);
+      f = uniform(f);
+      idx = uniform(idx);
+    }
+    if constexpr (S == 1) have = __builtin_amdgcn_readfirstlane(have && !fresh) != 0;
     bool search = false;  // the group's start goes on to a line search
     double ddir = 0.0;
     if (S == 1 || alive) do {
@@ -182,12 +216,16 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
       // -- value and gradient at xs (dual numbers, one direction per lane) ----
       double gn, fn;
       if (hi)
-        fn = group_value_grad<OBJ, G, double>(L, d, sh.xs, &gn);
+        fn = group_value_grad<OBJ, G, double>(L, d, sh.xs, &gn, known, S == 1 && have);
       else
-        fn = group_value_grad<OBJ, G, T>(L, d, sh.xs, &gn);
+        fn = group_value_grad<OBJ, G, T>(L, d, sh.xs, &gn, known, S == 1 && have);
 
       // y's and g'g are formed together (independent butterflies overlap);
       // right after a claim or an escalation y's is not used
+      if constexpr (kCut) {
+        gj = sh.vs[jv];
+        sj = sh.ss[jv];
+      }
       const double yj = gn - gj;  // zero beyond the dimension
       const double sy = lane_tree_sum<G, double>(yj * sj);
       const double gg = lane_tree_sum<G, double>(gn * gn);
@@ -199,25 +237,31 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
           // every lane: the tile sums cross lanes.  From 16 lanes on the tiles
           // take the vector by row broadcasts from the lanes' own entries.
           double uj;
-          if constexpr (kTileCols<G> == 16) {
+          if constexpr (kCut) {
+            sh.vs[jv] = yj;
+            wave_sync();
+            uj = H.matvec(scr, j);
+          } else if constexpr (kTileCols<G> == 16) {
             uj = H.matvec_bcast(yj);
           } else {
-            sh.vs[vpos<G>(j)] = yj;
+            sh.vs[jv] = yj;
             wave_sync();
             uj = H.matvec(sh.vs, j);
           }
           uj = own ? uj : 0.0;
           const double yu = lane_tree_sum<G, double>(yj * uj);
           if constexpr (kTileRows<G> > 1 || kTileCols<G> < 16) {  // rows of other lanes
-            sh.us[vpos<G>(j)] = uj;
-            sh.ss[vpos<G>(j)] = sj;
+            sh.us[jv] = uj;
+            if constexpr (!kCut) sh.ss[jv] = sj;
             wave_sync();
           }
           const double beta = (rho * rho) * yu + rho;
           // H+ = H - rho (s u' + u s') + beta s s'   (u = H y); inf * 0 would
           // have reached the padding when a coefficient is not finite
           bool fin;
-          if constexpr (kTileCols<G> == 16)
+          if constexpr (kCut)
+            fin = H.rank2(rho, beta, 2 * tile_vec_len(G), tile_vec_len(G), group_stride(G) - 2 * G, j, sj, uj);
+          else if constexpr (kTileCols<G> == 16)
             fin = H.rank2_bcast(rho, beta, sh.us, sh.ss, uj, sj, j, sj, uj);
           else
             fin = H.rank2(rho, beta, sh.us, sh.ss, j, sj, uj);
@@ -229,6 +273,7 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
       }
       gj = gn;
       f = fn;
+      if constexpr (kCut) xj = sh.xs[j];
       fresh = false;
       if (own && k < hot.trace_len) reqs[q.ri].trace[(idx * hot.trace_len + k) * d + j] = xj;
 
@@ -270,10 +315,14 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
 
       // -- search direction p = -H g (reset to -g if not a descent direction) -
       double hg;  // every lane: the tile sums cross lanes
-      if constexpr (kTileCols<G> == 16) {
+      if constexpr (kCut) {
+        sh.vs[jv] = gj;
+        wave_sync();
+        hg = H.matvec(scr, j);
+      } else if constexpr (kTileCols<G> == 16) {
         hg = H.matvec_bcast(gj);
       } else {
-        sh.vs[vpos<G>(j)] = gj;
+        sh.vs[jv] = gj;
         wave_sync();
         hg = H.matvec(sh.vs, j);
       }
@@ -294,9 +343,10 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
     if (S == 1 ? !search : __ballot(search) == 0ull) continue;
     wave_sync();
     int taken = -1;
+    have = false;
     if constexpr (kMixed) {
       if (__ballot(search && !hi) != 0ull) {
-        const int tk = wave_search<OBJ, G, G, TP, T>(L, hot, search && !hi, f, ddir, wave_lds, lay);
+        const int tk = wave_search<OBJ, G, G, TP, T>(L, hot, search && !hi, f, ddir, wave_lds, lay, known);
         if (search && !hi) {
           taken = tk;
           if (tk < 0) {
@@ -309,23 +359,29 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
       }
       if (__ballot(search && taken < 0) != 0ull) {
         const bool need = search && taken < 0;
-        const int tk = wave_search<OBJ, G, G, TP, double>(L, hot, need, f, ddir, wave_lds, lay);
+        const int tk = wave_search<OBJ, G, G, TP, double>(L, hot, need, f, ddir, wave_lds, lay, known);
         if (need) taken = tk;
       }
     } else {
-      taken = wave_search<OBJ, G, G, TP, double>(L, hot, search, f, ddir, wave_lds, lay);
+      taken = wave_search<OBJ, G, G, TP, double>(L, hot, search, f, ddir, wave_lds, lay, known);
     }
     wave_sync();  // every lane has read xs in the line search
+    have = !whole_form<E>::value && taken >= 0;
 
     // -- step: x_new = x + alpha p, s = x_new - x -----------------------------
     if (search) {
       const int nshrink = taken >= 0 ? taken : hot.iter_ls;
       ls_trials += taken >= 0 ? taken + 1 : hot.iter_ls;
       const double alpha = step_length(sh.al, q.shrink, nshrink);
+      if constexpr (kCut) {
+        xj = sh.xs[j];
+        pj = sh.ps[j];
+      }
       const double xnew = xj + alpha * pj;
       sj = own ? xnew - xj : 0.0;
       xj = own ? xnew : 0.0;
       sh.xs[j] = xj;
+      if constexpr (kCut) sh.ss[jv] = sj;
     }
   }
 }

@@ -272,6 +272,36 @@ __device__ __forceinline__ void upd_bcast(double &x0, double &x1, double &x2, do
         "v"(e[2]), "v"(e[3]), "n"(K));
 }
 
+// The same for three rows whose columns lie in different blocks, each with its
+// own register of vector entries.
+template <int K>
+__device__ __forceinline__ void fmac_bcast3(double (&a)[3], const double (&v)[3], double h0, double h1,
+                                            double h2) {
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %3, %6 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %4, %7 row_newbcast:%9 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %5, %8 row_newbcast:%9 row_mask:0xf bank_mask:0xf"
+      : "+v"(a[0]), "+v"(a[1]), "+v"(a[2])
+      : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(h0), "v"(h1), "v"(h2), "n"(K));
+}
+template <int K>
+__device__ __forceinline__ void upd_bcast3(double &x0, double &x1, double &x2, const double (&u)[3],
+                                           const double (&s)[3], const double (&a)[3],
+                                           const double (&e)[3]) {
+  asm volatile(
+      "s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %3, %9 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %4, %10 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %5, %11 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, %6, %12 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %7, %13 row_newbcast:%15 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %8, %14 row_newbcast:%15 row_mask:0xf bank_mask:0xf"
+      : "+v"(x0), "+v"(x1), "+v"(x2)
+      : "v"(u[0]), "v"(u[1]), "v"(u[2]), "v"(s[0]), "v"(s[1]), "v"(s[2]), "v"(a[0]), "v"(a[1]),
+        "v"(a[2]), "v"(e[0]), "v"(e[1]), "v"(e[2]), "n"(K));
+}
+
 template <int G>
 constexpr int kTileCols = G < 16 ? G : 16;
 template <int G>
@@ -483,6 +513,124 @@ struct Tile {
   }
 };
 
+// The inverse Hessian of a start with d <= kCutDim on 64 lanes, without most of
+// the 64 x 64 padding: 52 doubles per lane instead of 64.  The first three
+// 16-lane rows hold the column blocks 0, 1 and 2 of rows 0 .. 47 (lane 16 p + i:
+// block p of rows i, 16 + i, 32 + i); the last holds the blocks 0, 1 and 2 of row
+// 48 + i; and lane r holds the four columns 48 .. 51 of row r.
+// Sums as in Tile: a fused multiply-add chain per block, the blocks pairwise.
+// 104 VGPRs of H instead of 128 let a SIMD hold three of the wavefronts instead
+// of two, and 208 instead of 256 multiply-adds an iteration are left.
+//
+// The vectors it multiplies lie unpadded in the group's LDS, and the products
+// cross lanes through kCutScratch doubles there.
+constexpr int kCutScratch = 3 * 64;
+struct CutTile {
+  double h[48];  // [chain][column]
+  double x[4];   // columns 48 .. 51 of row j
+  // Where the lane reads and writes, for a vector v (chain t):
+  //   entry of its column block   first 16 rows: v[j];  last: v[16 t + i]
+  //   entry of its row            first 16 rows: v[16 t + i];  last: v[j]
+  //   place of its partial sum    [block][row]
+  const double *low;  // v[i]
+  double *own;        // v[j]
+  double *part;
+  __device__ __forceinline__ void place(double *v, double *scr, int j) {
+    const bool m = j < 48;
+    low = v + (j & 15);
+    own = v + j;
+    part = scr + (m ? 64 * (j >> 4) + (j & 15) : j);
+  }
+  __device__ __forceinline__ static int row_of(int j, int t) { return j < 48 ? 16 * t + (j & 15) : j; }
+  __device__ __forceinline__ static int col_of(int j, int t) { return 16 * (j < 48 ? j >> 4 : t); }
+
+  __device__ __forceinline__ void identity(int j) {
+    j = Tile<64>::opaque(j);
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int k = 0; k < 16; ++k) h[16 * t + k] = row_of(j, t) == col_of(j, t) + k ? 1.0 : 0.0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) x[k] = j == 48 + k ? 1.0 : 0.0;
+  }
+  __device__ __forceinline__ void restore_padding(int j, int d) {
+    j = Tile<64>::opaque(j);
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const int r = row_of(j, t), c = col_of(j, t) + k;
+        if (r >= d || c >= d) h[16 * t + k] = r == c ? 1.0 : 0.0;
+      }
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (j >= d || 48 + k >= d) x[k] = j == 48 + k ? 1.0 : 0.0;
+  }
+  // (H v)_j for the vector the lane is placed at; scr as in place.
+  __device__ __forceinline__ double matvec(const double *scr, int j) const {
+    const bool m = Tile<64>::opaque(j) < 48;  // (kept, the addresses would cost registers)
+    const double *ent = m ? own : low;
+    const int step = m ? 0 : 16;
+    const double ve[3] = {ent[0], ent[step], ent[2 * step]}, vx = low[48];
+    double p[3] = {0.0, 0.0, 0.0}, px = 0.0;
+    static_for<0, 16>([&](auto kk) {
+      constexpr int k = decltype(kk)::value;
+      fmac_bcast3<k>(p, ve, h[k], h[16 + k], h[32 + k]);
+    });
+    static_for<0, 4>([&](auto kk) {
+      constexpr int k = decltype(kk)::value;
+      fmac_bcast<k>(px, vx, x[k]);
+    });
+#pragma unroll
+    for (int t = 0; t < 3; ++t) part[t * (16 + 3 * step)] = p[t];
+    wave_sync();
+    return (scr[j] + scr[64 + j]) + (scr[128 + j] + px);
+  }
+  // The rank-2 update, as Tile::rank2; s and u lie so and uo doubles behind the
+  // vector the lane is placed at, whose place and the one eo doubles behind it
+  // take the rows' coefficients (read back for the lane's three rows: forming
+  // them there again took 9 FP64 operations more).  False when a coefficient of
+  // any row is not finite (the same on all lanes).
+  __device__ __forceinline__ bool rank2(double rho, double beta, int uo, int so, int eo, int j,
+                                        double sj, double uj) {
+    const bool m = Tile<64>::opaque(j) < 48;
+    const double *ent = m ? own : low, *row = m ? low : own;
+    const int step = m ? 0 : 16;
+    double a[3], e[3], u[3], s[3];
+    const double ax = -rho * sj, ex = beta * sj - rho * uj;
+    own[0] = ax;
+    own[eo] = ex;
+    wave_sync();
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const double *q = row + t * (16 - step);
+      a[t] = q[0];
+      e[t] = q[eo];
+      u[t] = ent[uo + t * step];
+      s[t] = ent[so + t * step];
+    }
+    static_for<0, 16>([&](auto kk) {
+      constexpr int k = decltype(kk)::value;
+      upd_bcast3<k>(h[k], h[16 + k], h[32 + k], u, s, a, e);
+    });
+    const double ux = low[48 + uo], sx = low[48 + so];
+    static_for<0, 4>([&](auto kk) {
+      constexpr int k = decltype(kk)::value;
+      upd_bcast<k>(x[k], ux, sx, ax, ex);
+    });
+    return __ballot(!(__builtin_isfinite(ax) && __builtin_isfinite(ex))) == 0ull;
+  }
+};
+
+template <int G, bool kCut>
+struct NarrowTile {
+  using type = Tile<G>;
+};
+template <>
+struct NarrowTile<64, true> {
+  using type = CutTile;
+};
+
 // Value of the objective at the point whose coordinates are xs[0..d-1] in the
 // group's LDS, evaluated in number type T.  The group covers G * CPL term
 // slots: lane c evaluates the terms CPL c .. CPL c + CPL - 1 (zero past the
@@ -529,9 +677,14 @@ __device__ __forceinline__ double group_value(const GroupLanes<G> &L, int d, con
 // sums.  Every other term of Alg. 5's pass j has a zero tangent, and with at
 // most two nonzero tangents (window W <= 2) the pairwise sum of pass j adds
 // exactly these, so lane j gets the tangent of the full pass j.
+//
+// known, when have (the same on all lanes), holds the term sums of the trial of
+// the line search that produced xs in the same number type: the same terms over
+// the same pairwise tree, so the value's butterfly is skipped.
 template <int OBJ, int G, class T>
 __device__ __forceinline__ double group_value_grad(const GroupLanes<G> &L, int d,
-                                                   const double *xs, double *gj) {
+                                                   const double *xs, double *gj,
+                                                   const double *known = nullptr, bool have = false) {
   using E = Elem<OBJ>;
   const int j = L.j;
   if constexpr (whole_form<E>::value) {
@@ -572,7 +725,10 @@ __device__ __forceinline__ double group_value_grad(const GroupLanes<G> &L, int d
   }
   dual<T> sd[E::K];
 #pragma unroll
-  for (int k = 0; k < E::K; ++k) sd[k] = dual<T>{lane_tree_sum<G, T>(val[k]), tan[k]};
+  for (int k = 0; k < E::K; ++k) sd[k] = dual<T>{have ? (T)known[k] : T(0), tan[k]};
+  if (!have)
+#pragma unroll
+    for (int k = 0; k < E::K; ++k) sd[k].v = lane_tree_sum<G, T>(val[k]);
   const dual<T> r = E::template outer<dual<T>>(d, sd);
   *gj = (j < d) ? (double)r.t : 0.0;
   return (double)r.v;

@@ -85,3 +85,38 @@ def test_blocks_diverging_starts(Z, ctx, oracle_mod, monkeypatch, lanes, d):
     o = oracle_mod.bfgs(p, oracle_mod.pso(p)["x"])
     for k in ("f", "x", "iters", "status", "ls_trials", "resets"):
         assert _same(g[k], o[k]), k
+
+
+@pytest.mark.parametrize("d", [1, 4, 16, 33, 47, 48, 49, 50, 51, 52])
+@pytest.mark.parametrize("objective,iter_ls", [("rosenbrock", 20), ("rosenbrock", 1),
+                                               ("styblinski_tang", 20), ("quartic", 3)])
+def test_cut_tile(Z, ctx, oracle_mod, monkeypatch, d, objective, iter_ls):
+    # more starts than two wavefronts on each SIMD of one unit: the kernel with
+    # the cut tile.  One trial per search lets the starts run off (as above).
+    monkeypatch.setenv("ZEUS_TILE_LANES", "52")
+    monkeypatch.setenv("ZEUS_BFGS_CUS", "1")
+    p = W.problem(objective=objective, dim=max(d, 2) if objective == "rosenbrock" else d, n=14,
+                  lower=-2.0, upper=2.0, iter_pso=1, iter_bfgs=60, iter_ls=iter_ls, seed=d)
+    print(f"\n[blocks] cut {objective} d={d} ls={iter_ls}", flush=True)
+    g = Z.zeus_minimize(ctx, p)
+    o = oracle_mod.bfgs(p, oracle_mod.pso(p)["x"])
+    for k in ("f", "x", "iters", "status", "ls_trials", "resets"):
+        assert _same(g[k], o[k]), k
+    ended = o["status"] != 3  # not at a value that is not finite
+    assert _same(g["skips"][ended], o["skips"][ended])
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_cut_tile_or_not(Z, ctx, monkeypatch, precision):
+    # one request through the cut tile and through the whole one, and two
+    # dimensions and an early stop in one launch
+    ps = [W.problem(objective="rosenbrock", dim=d, n=n, lower=-2.0, upper=2.0, iter_pso=1,
+                    iter_bfgs=30, seed=3, request_id=i, precision=precision, required_converged=c)
+          for i, (d, n, c) in enumerate(((50, 1500, 0), (35, 900, 0), (48, 290, 5)))]
+    print(f"\n[blocks] cut or not {precision}", flush=True)
+    cut = Z.zeus_minimize_batch(ctx, ps)
+    monkeypatch.setenv("ZEUS_TILE_LANES", "64")
+    for p, g in zip(ps, cut):
+        whole = Z.zeus_minimize(ctx, p)
+        for k in KEYS:
+            assert _same(g[k], whole[k]), (p["dim"], k)
