@@ -6,7 +6,7 @@ For every objective, precision and probe dimension it times each candidate
 tiling of the BFGS phase:
   * one group of G lanes per start, G a power of two from max(4, next_pow2(d))
     up to 64 (H in registers, 64/G starts per wavefront);
-  * one 256-lane block per start (H in a device-memory slot).
+  * one block per start with a part of H in a device-memory slot.
 Every tiling computes the same pairwise sums, so the tuner also checks that
 all candidates return bit-identical results.  The fastest tiling of each probe
 dimension covers the dimensions from the previous probe (exclusive) up to it;

@@ -185,14 +185,15 @@ hipError_t launch_prec(const Group &g, int64_t want, int cus) {
 // not for user objectives, which have a lane per coordinate of 128),
 // kTileBlockDim (four wavefronts, dim <= 128), kHybridDim (one block of eight
 // wavefronts per start, H in their registers and LDS, dim <= 208) or kWideLanes
-// (one block per start, H in device memory).
+// (one block of eight wavefronts per start, H in registers, LDS and a slot in
+// device memory).
 // Every tiling computes the same pairwise trees, so results do not depend on
 // it; only speed does.  The rules come from the autotuner's table; a start
 // no rule covers gets the smallest power of two >= max(dim, 4), or above 64
-// dimensions the block with H on chip (in registers up to 128, in registers
-// and LDS up to 208; the device-memory block above).  A user objective up to 8 dimensions gets 32 lanes:
-// evaluated as a whole it tries one step length per lane in a line-search
-// round, and on four user sources (d = 2..5, 1.9 to 12 trials per iteration)
+// dimensions the first block that holds it.  Where the table says 64 lanes the
+// cut tile is taken if it can be (measured in launch_obj).  A user objective up
+// to 8 dimensions gets 32 lanes: evaluated as a whole it tries one step length
+// per lane in a line-search round, and on four user sources (d = 2..5, 1.9 to 12 trials per iteration)
 // 32 lanes took 0.71 of the time of the smallest group in geometric mean.
 // ZEUS_TILE_LANES forces a tiling (the autotuner uses it to time the
 // candidates).

@@ -7,7 +7,8 @@
 //    a 64-lane wavefront holds 64/G groups, a 256-thread block four waves;
 //  * lane j owns coordinate j; the inverse Hessian H stays in the group's
 //    registers for the whole run (H never touches HBM), in tiles of R rows by
-//    16 columns (zeus_group.h Tile);
+//    16 columns (zeus_group.h Tile), or up to 52 dimensions in the cut tile
+//    (CutTile), whose vectors the lanes take from LDS;
 //  * gradient: lane j evaluates on dual numbers seeded with the tangent e_j,
 //    so the G lanes compute the dim passes of Alg. 5 at once;
 //  * line search: each round evaluates consecutive trials of the
@@ -88,8 +89,8 @@ __device__ __forceinline__ V uniform(V v) {
 // cut tile exists for its third wave (VALU active 80 -> 85 % of the time at 7 %
 // fewer instructions: Rosenbrock d = 50, 131,072 starts, 57.1 -> 48.2 ms), for
 // which the kernel keeps x, g, p and s in LDS between their uses and the start's
-// counters in scalar registers.  Other kernels reach their occupancy without the request, and
-// user code is of unknown size.
+// counters in scalar registers.  Other kernels reach their occupancy without the
+// request, and user code is of unknown size.
 template <int OBJ, int G, bool kCut = false>
 constexpr int kBfgsWaves = kCut ? 3
                            : G == 64 ? 2

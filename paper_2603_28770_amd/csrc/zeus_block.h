@@ -1,5 +1,5 @@
 // zeus_block.h -- pieces shared by the block-per-start BFGS kernels (64 < d):
-// one block of four or eight wavefronts runs a start.
+// one block of three, four or eight wavefronts runs a start.
 // Lane j owns coordinate j; the block exchanges vectors through its LDS
 // struct (a type with the members these helpers name: xs, ps, red, tsum,
 // pass, al and q) and finishes every sum across its wavefronts there.
@@ -8,10 +8,6 @@
 #include "zeus_bfgs_common.h"
 
 namespace zeus {
-
-constexpr int kBlockLanes = kWideLanes;     // lanes (threads) per start (four wavefronts)
-constexpr int kBlockWaves = kBlockLanes / 64;  // wavefronts per start == trials per round
-static_assert(kBlockWaves == 4, "the device-memory and on-chip blocks have four wavefronts");
 
 // The wavefronts of the block (3, 4 or 8), from the LDS struct's sum slots.
 template <class Shm>
@@ -28,7 +24,7 @@ constexpr int shm_waves() {
 template <int K, class T, class Shm>
 __device__ __forceinline__ void block_tree_sums(T (&v)[K], Shm &sh, int &phase) {
   constexpr int NW = shm_waves<Shm>();
-  static_assert(NW == 4 || NW == 8, "blocks of four or eight wavefronts");
+  static_assert(NW == 8, "the sums of eight wavefronts");
   static_assert(K <= (int)(sizeof(Shm::red[0]) / sizeof(Shm::red[0][0])),
                 "more sums than the LDS struct has slots for");
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -41,12 +37,8 @@ __device__ __forceinline__ void block_tree_sums(T (&v)[K], Shm &sh, int &phase) 
 #pragma unroll
   for (int k = 0; k < K; ++k) {
     const double *r = sh.red[phase][k];
-    const T lo = ((T)r[0] + (T)r[1]) + ((T)r[2] + (T)r[3]);
-    if constexpr (NW == 4) {
-      v[k] = lo;
-    } else {
-      v[k] = lo + (((T)r[4] + (T)r[5]) + ((T)r[6] + (T)r[7]));
-    }
+    v[k] = (((T)r[0] + (T)r[1]) + ((T)r[2] + (T)r[3])) +
+           (((T)r[4] + (T)r[5]) + ((T)r[6] + (T)r[7]));
   }
   phase ^= 1;
 }

@@ -16,12 +16,12 @@ namespace zeus {
 // registers, 32 columns each; up to kTileBlockDim a block of four runs a start
 // with H in the registers of its wavefronts, a 64 x 64 quarter each; up to
 // kHybridDim a block of eight wavefronts runs a start with eight 64 x 64 tiles
-// of H in its registers and the rest in LDS; above that a block of kWideLanes
-// lanes runs a start with the rows in a device-memory slot of the block.  As a
+// of H in its registers and the rest in LDS; above that a block of eight runs a
+// start with H in their registers, LDS and a slot in device memory.  As a
 // tiling (lanes per start, below), kCutDim names 64 lanes whose H leaves out
 // most of the padding of 64 x 64 (d <= 52), kTile3Dim and kTileBlockDim name
 // the blocks of three and four wavefronts with H in registers, kHybridDim the
-// register-and-LDS block and kWideLanes the device-memory one.
+// register-and-LDS block and kWideLanes the one with a slot.
 constexpr int kMaxDim = 256;
 constexpr int kMaxNarrowDim = 64;
 constexpr int kCutDim = 52;
@@ -197,8 +197,8 @@ size_t lbfgs_lds_bytes(int slots);
 // most 64; kCutDim for 64 lanes and the cut tile, d <= 52; kTile3Dim,
 // kTileBlockDim for one block per start with H in registers, d <= 96, 128;
 // kHybridDim for one block per start with H in registers and LDS, d <= 208;
-// kWideLanes for one block per start with H in device memory), from the tiling
-// table.
+// kWideLanes for one block per start with a part of H in a device-memory slot),
+// from the tiling table.
 int group_lanes(int objective, int precision, int dim);
 
 // One rule of the tiling table: problems of this objective and precision
