@@ -79,10 +79,12 @@ __device__ __forceinline__ int request_of(const ReqDev *reqs, int nreq, int64_t 
 }
 
 // sqrt(gg) < bound, the norm test of a start (gg = g'g), decided exactly as
-// written but without the square root when gg >= 4 bound^2: there the root
-// is at least twice the bound up to a few roundings, so the test fails.
+// written but without the square root when gg >= 4 bound^2 and gg is not
+// subnormal: there the root is at least twice the bound up to a few roundings,
+// so the test fails.  (Below a bound of about 1e-154 the square loses its digits
+// and then vanishes, and says nothing about a subnormal or zero gg.)
 __device__ __forceinline__ bool norm_below(double gg, double bound) {
-  const bool near = gg < (4.0 * bound) * bound;
+  const bool near = gg < (4.0 * bound) * bound || gg < 0x1p-1022;
   if (__ballot(near) == 0ull) return false;  // (per lane, the root would be taken every time)
   if (!near) return false;
   return sqrt(gg) < bound;
