@@ -175,7 +175,11 @@ __device__ __forceinline__ void sincos(double x, double &s, double &c) {
 __device__ __forceinline__ double exp(double x) {
   // no branch: outside the range the polynomial is meaningless and the result
   // is replaced at the end
-  const double k = __builtin_rint(x * kLog2e);  // x = k ln2 + r
+  // x = k ln2 + r, k the integer nearest to x log2 e: adding 1.5 2^52 rounds to it
+  // and leaves it in the low bits (some bits for a NaN, which no conversion to an
+  // integer defines)
+  const double big = x * kLog2e + 0x1.8p52, k = big - 0x1.8p52;
+  const int n = (int)(uint32_t)__builtin_bit_cast(uint64_t, big);
   double r = __builtin_fma(-k, kLn2A, x);
   r = __builtin_fma(-k, kLn2B, r);
   double p = 1.0 / 6227020800.0;
@@ -193,7 +197,7 @@ __device__ __forceinline__ double exp(double x) {
   p = __builtin_fma(p, r, 1.0);
   p = __builtin_fma(p, r, 1.0);
   // NaN compares false and keeps its k, remainder and polynomial NaN
-  const double e = __builtin_ldexp(p, (int)k);
+  const double e = __builtin_ldexp(p, n);
   return x > 710.0 ? __builtin_huge_val() : x < -746.0 ? 0.0 : e;
 }
 }  // namespace zm
