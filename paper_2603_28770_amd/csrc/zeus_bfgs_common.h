@@ -343,10 +343,10 @@ __device__ __forceinline__ int wave_search(const GroupLanes<G> &L, const HotRegs
   {
     do {
       const int t = base + r;
-      // (whole form: lanes past the last trial take none, which spares them
-      // the step lengths past the table)
-      const bool tries = !whole_form<E>::value || t < iter_ls;
-      const double alpha = tries ? step_length(own + lay.al, oq.shrink, t) : 0.0;
+      // lanes past the last trial take a length that costs nothing, and in whole
+      // form no value either (a round of one start's lanes reaches far past it)
+      const bool tries = t < iter_ls;
+      const double alpha = step_length(own + lay.al, oq.shrink, tries ? t : 0);
       // the trial's bound, formed before the terms rather than behind them
       const double bound = f + (hot.armijo_c * alpha) * ddir;
       double ft = 0.0;
@@ -357,7 +357,7 @@ __device__ __forceinline__ int wave_search(const GroupLanes<G> &L, const HotRegs
       } else {
         ft = trial_value<OBJ, SLOTS, TP, U>(own + lay.xs, own + lay.ps, alpha, oq.d, oq.m, c, sums);
       }
-      const bool ok = open & (t < iter_ls) & (ft <= bound);
+      const bool ok = open & tries & (ft <= bound);
       const uint64_t mine = L.ballot(ok) & leaders;
       if (mine != 0ull) {
         const int first = (__ffsll((unsigned long long)mine) - 1) / TP;  // the passing trial's place
@@ -407,8 +407,8 @@ __device__ __forceinline__ int wave_search(const GroupLanes<G> &L, const HotRegs
       const ReqHot &q = *reinterpret_cast<const ReqHot *>(sl + lay.q);
       const int t = base + ((lane / TP) & (per - 1));
       const int target_ls = q.iter_ls;
-      const bool tries = !whole_form<E>::value || t < target_ls;
-      const double alpha = tries ? step_length(sl + lay.al, q.shrink, t) : 0.0;
+      const bool tries = t < target_ls;
+      const double alpha = step_length(sl + lay.al, q.shrink, tries ? t : 0);
       const double bound = sl[lay.fd] + (q.armijo_c * alpha) * sl[lay.fd + 1];
       double ft = 0.0;
       U sums[E::K];
@@ -417,7 +417,7 @@ __device__ __forceinline__ int wave_search(const GroupLanes<G> &L, const HotRegs
       } else {
         ft = trial_value<OBJ, SLOTS, TP, U>(sl + lay.xs, sl + lay.ps, alpha, q.d, q.m, c, sums);
       }
-      const bool ok = valid & (t < target_ls) & (ft <= bound);
+      const bool ok = valid & tries & (ft <= bound);
       const uint64_t hits = __ballot(ok) & all_leaders;
       const uint64_t field = share == 6 ? ~0ull : (1ull << (1 << share)) - 1ull;  // a share's lanes
       if constexpr (!whole_form<E>::value) {
