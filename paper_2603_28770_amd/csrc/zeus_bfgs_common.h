@@ -78,22 +78,27 @@ __device__ __forceinline__ int request_of(const ReqDev *reqs, int nreq, int64_t 
   return lo;
 }
 
-// sqrt(gg) < bound, the norm test of a start (gg = g'g), decided exactly as
-// written but without the square root when gg >= 4 bound^2 and gg is not
-// subnormal: there the root is at least twice the bound up to a few roundings,
-// so the test fails.  (Below a bound of about 1e-154 the square loses its digits
-// and then vanishes, and says nothing about a subnormal or zero gg.)
+// sqrt(gg) < bound, the norm test of a start (gg = g'g).  kWave: the starts of
+// the wave nearly always fail it together (one start per wave, above all); then
+// a branch skips the root when gg >= 4 bound^2: there it is at least twice the
+// bound up to a few roundings.  (Below a bound of about 1e-154 the square loses
+// its digits and then vanishes, so a subnormal or zero gg always goes to the
+// root.)  With many starts in a wave the branch costs more than the root
+// (Rosenbrock d = 4, 256 starts 0.193 -> 0.188 ms).
+template <bool kWave = true>
 __device__ __forceinline__ bool norm_below(double gg, double bound) {
-  const bool near = gg < (4.0 * bound) * bound || gg < 0x1p-1022;
-  if (__ballot(near) == 0ull) return false;  // (per lane, the root would be taken every time)
-  if (!near) return false;
+  if constexpr (kWave)
+    if (__ballot(gg < __builtin_fmax((4.0 * bound) * bound, 0x1p-1022)) == 0ull) return false;
   return sqrt(gg) < bound;
 }
 
 // Relaxed agent-scope access to the early-stop state: its values are only
 // ever bounds (a stale bound is a larger one), so no ordering is needed.
 __device__ __forceinline__ int es_load(const int32_t *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // as device memory, not a generic address: a generic load would also count as
+  // an LDS access, and every later LDS read would wait for it
+  typedef const __attribute__((address_space(1))) int32_t *Global;
+  return __hip_atomic_load((Global)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Smallest iteration k at which the counts of the Fenwick tree (nodes
@@ -213,6 +218,26 @@ struct HotRegs {
   }
 };
 
+// Objectives with starts that stall: near a minimum their value is a small
+// difference of larger numbers, so at some point no trial passes any more and a
+// start whose gradient is still above the tolerance fails every search to its
+// budget.  Where the minimum is zero the value keeps its relative precision.
+template <int OBJ>
+constexpr bool kStalls = !(OBJ == kRosenbrock || OBJ == kSphere || OBJ == kQuartic);
+
+// Whether the groups of a BFGS wave share their lanes in the line searches
+// (wave_search).  That helps the starts that stall, and costs the others the
+// loop that keeps a wave's groups together: where nothing stalls each group
+// searches, claims and ends by itself (Rosenbrock, shared and by itself: d = 4,
+// 1,024 starts 0.227 and 0.207 ms; d = 14 in mixed precision, 65,536 starts 1.83
+// and 1.72 ms).  Two groups of 32 lanes gain little: nothing in whole form, where 32
+// lanes already try 32 lengths (a user's chain of 20 terms, 32,768 starts: 0.92 of
+// the speed), and less than they pay for Styblinski-Tang (d = 24, 65,536 starts
+// 1.37 and 1.31 ms), but a third for Ackley (d = 18, 4,096 starts 4.8 and 6.3 ms).
+template <int OBJ, int G>
+constexpr bool kShareLanes = G < 64 && kStalls<OBJ> &&
+                             !(G == 32 && (whole_form<Elem<OBJ>>::value || OBJ == kStyblinskiTang));
+
 // Lanes per line-search trial.  A lane then holds SLOTS / TP consecutive term
 // slots, and a round gives a group of G lanes R = G / TP trials.  64-lane
 // groups take R = 2 (one trial a round was slower, four evaluate trials past
@@ -265,10 +290,13 @@ __device__ __forceinline__ double trial_value(const double *xs, const double *ps
         const int ie = i + e < SLOTS ? i + e : SLOTS - 1;
         w[e] = (U)(xs[ie] + alpha * ps[ie]);
       }
-      // With a trial per lane, slot b is term b on every lane: no lane of
-      // the wave may need it (d = 2 and 3 in groups of four lanes)
+      // With a trial per lane, slot b is term b on every lane, and no lane of
+      // the wave may need it (d = 2 and 3 in groups of four lanes).  Asking costs
+      // more than a polynomial term (Rosenbrock d = 4, 256 starts 0.193 and 0.202
+      // ms), not more than the others (Rastrigin d = 3, 1,024 starts 2.91 and 2.72).
+      constexpr bool kAsk = TP == 1 && (OBJ == kRastrigin || OBJ == kAckley || OBJ == kGoldsteinPrice);
       bool any = true;
-      if constexpr (TP == 1)
+      if constexpr (kAsk)
         if (b > 0) any = __ballot(i < m) != 0ull;
 #pragma unroll
       for (int kk = 0; kk < E::K; ++kk) tv[kk][b] = U(0);
@@ -295,15 +323,16 @@ __device__ __forceinline__ double read_lane(double v, int lane) {
 }
 
 // The Armijo searches (Alg. 6) of a wave's groups, the objective evaluated in
-// number type U.  Every lane of the wave must call it; need (the same on all
-// lanes of a group) says which groups search, the others lend their lanes;
+// number type U.  With SHARE every lane of the wave must call it and need (the
+// same on all lanes of a group) says which groups search, the others lending
+// their lanes; without, the lanes of each searching group call it by themselves.
 // hot, f and ddir are the scalars, the value and g'p of the lane's own group.
 // Returns, on the lanes of a searching group, the index of the first trial
 // that passes, or -1 when none of the iter_ls trials does: the step the
 // sequential loop of Alg. 6 returns.
 //
 // A round evaluates 64 / TP trials, TP lanes each.  While more than half of
-// the wave's groups search, each tries R = G / TP trials a round on its own
+// the wave's groups search (always, without SHARE), each tries R = G / TP trials a round on its own
 // lanes.  After that the lanes are shared out among the groups that have not
 // found their step (as many equal shares as the next power of two), so the
 // fewer they are the more trials each tries at once.  A start that stalls,
@@ -311,20 +340,20 @@ __device__ __forceinline__ double read_lane(double v, int lane) {
 // with its own lanes alone it took 5 rounds an iteration beside idle ones.
 // Bound by latency there.  BFGS phase with fixed lanes and with shared ones:
 // Ackley d = 10, 16,384 starts 15.9 -> 7.4 ms, Rastrigin d = 6, 16,384 starts
-// 5.5 -> 3.4 ms, d = 2, 65,536 starts 9.2 -> 8.1 ms; where no start stalls the
-// test after each round costs 0-4% (Rosenbrock d = 2, 65,536 starts 1.25 -> 1.27 ms).
+// 5.5 -> 3.4 ms, d = 2, 65,536 starts 9.2 -> 8.1 ms.  (Where no start stalls it
+// costs up to a tenth, see kShareLanes.)
 // Sharing from the first failed round on, whatever the number of groups left,
 // was slower (Ackley d = 2, 4,096 starts 9.4 ms against 7.6), and so was
 // sharing after two rounds (Rastrigin d = 6 4.3 ms).
 //
 // The group sees what is written to acc after its next wave_sync.  kept, where a
 // wave has one group, receives the accepted trial's term sums on every lane.
-template <int OBJ, int G, int SLOTS, int TP, class U>
+template <int OBJ, int G, int SLOTS, int TP, bool SHARE, class U>
 __device__ __forceinline__ int wave_search(const GroupLanes<G> &L, const HotRegs<G> &hot, bool need,
                                            double f, double ddir, double *wave_lds,
                                            const SearchLayout &lay, double *kept = nullptr) {
   using E = Elem<OBJ>;
-  constexpr int R = G / TP, S = 64 / G;
+  constexpr int R = G / TP, S = SHARE ? 64 / G : 1;  // S: groups that share lanes
   static_assert(TP >= 1 && TP <= G && G % TP == 0 && SLOTS % TP == 0, "whole trials per group");
   static_assert(E::K <= kMaxSums, "more term sums than the slots kept for them");
   const int lane = threadIdx.x & 63, c = lane % TP;
@@ -368,12 +397,12 @@ __device__ __forceinline__ int wave_search(const GroupLanes<G> &L, const HotRegs
 #pragma unroll
             for (int kk = 0; kk < E::K; ++kk)
               wave_lds[L.grp * lay.stride + lay.acc + kk] = (double)sums[kk];
-        if constexpr (S == 1 && !whole_form<E>::value) {
+        if constexpr (G == 64 && !whole_form<E>::value) {
           if (kept)
 #pragma unroll
             for (int kk = 0; kk < E::K; ++kk) kept[kk] = read_lane((double)sums[kk], first * TP);
         }
-        if constexpr (S == 1) return taken;  // the wave's only group (mine is a scalar there)
+        if constexpr (S == 1) return taken;
       }
       base += R;
       open = open && base < iter_ls;

@@ -124,6 +124,8 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
   constexpr SearchLayout lay = group_search_layout(G, kCut);
   double *scr = wave_lds + group_stride(G);  // the cut tile's (one group per wave)
   constexpr int TP = kTrialLanes<OBJ, G>;
+  constexpr bool kShare = kShareLanes<OBJ, G>;
+  constexpr bool kOwn = S > 1 && !kShare;  // every group of the wave goes its own way
 
   bool own = false;
   const int jv = kCut ? j : vpos<G>(j);
@@ -145,8 +147,9 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
 
   for (;;) {
     // -- claim a start when idle ------------------------------------------
-    // A group without starts left stays in the loop until its whole wave is
-    // done: its lanes serve the searches of the wave's other groups.
+    // With shared searches a group without starts left stays in the loop until
+    // its whole wave is done: its lanes serve the wave's other groups.
+    bool skipped = false;
     while (alive && idx < 0) {
       // the first start of a group is its own index; later ones come from
       // the counter, after the starts taken that way
@@ -172,7 +175,9 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
       idx = (int64_t)got - rq.start_offset + rq.slice_first;
       if (es_pass == 2 && !es_rerun(rq, idx)) {  // keeps its first-pass result
         idx = -1;
-        continue;
+        if constexpr (!kOwn) continue;
+        skipped = true;
+        break;
       }
       const int d0 = rq.d;
       if (ri != cur_ri) {  // the LDS slice still holds the previous start's request
@@ -192,8 +197,10 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
       ls_trials = 0;
       fresh = true;
       hi = !kMixed;
+      if constexpr (kOwn) break;
     }
-    if (S == 1 ? !alive : __ballot(alive) == 0ull) break;
+    if (kOwn && skipped) continue;
+    if (kShare ? __ballot(alive) == 0ull : !alive) break;
     wave_sync();
     const ReqHot &q = *sh.q;
     const int d = hot.d;
@@ -208,11 +215,13 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
     if constexpr (S == 1) have = __builtin_amdgcn_readfirstlane(have && !fresh) != 0;
     bool search = false;  // the group's start goes on to a line search
     double ddir = 0.0;
-    if (S == 1 || alive) do {
-      // the group's stopping bound, read early (its use is at the termination
-      // test) and taken from one lane: the bound falls while the kernel runs
+    if (!kShare || alive) do {
+      // the group's stopping bound, read early; taken from one lane at the
+      // termination test (the bound falls while the kernel runs), so that the
+      // evaluation does not wait for the load
       int bound = 0x7fffffff;
-      if (hot.es) bound = __shfl(es_load(q.es + kEsBound), L.grp * G, 64);
+      if (hot.es) bound = es_load(q.es + kEsBound);
+      if constexpr (S == 1) bound = __builtin_amdgcn_readfirstlane(bound);
 
       // -- value and gradient at xs (dual numbers, one direction per lane) ----
       double gn, fn;
@@ -281,15 +290,16 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
       // -- termination: non-finite, ||g|| < Theta, budget ---------------------
       const bool bad = (own && !__builtin_isfinite(gj)) || !__builtin_isfinite(f);
       const bool any_bad = L.ballot(bad) != 0ull;
-      if (kMixed && !hi && (any_bad || norm_below(gg, 10.0 * hot.tol))) {
+      if (kMixed && !hi && (any_bad || norm_below<(G == 64)>(gg, 10.0 * hot.tol))) {
         hi = true;  // escalate: re-evaluate this point in FP64
         fresh = true;
         break;
       }
+      if (S > 1 && hot.es) bound = __shfl(bound, L.grp * G, 64);
       int status = -1;
       if (any_bad)
         status = ZEUS_ST_NONFINITE;
-      else if (norm_below(gg, hot.tol))
+      else if (norm_below<(G == 64)>(gg, hot.tol))
         status = ZEUS_ST_CONVERGED;
       else
         status = budget_status(q, hot.iter_bfgs, k, bound);
@@ -340,14 +350,14 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
       search = true;
     } while (false);
 
-    // -- Armijo backtracking (Alg. 6), by every lane of the wave --------------
-    if (S == 1 ? !search : __ballot(search) == 0ull) continue;
+    // -- Armijo backtracking (Alg. 6), with shared lanes by every lane of the wave
+    if (kShare ? __ballot(search) == 0ull : !search) continue;
     wave_sync();
     int taken = -1;
     have = false;
     if constexpr (kMixed) {
-      if (__ballot(search && !hi) != 0ull) {
-        const int tk = wave_search<OBJ, G, G, TP, T>(L, hot, search && !hi, f, ddir, wave_lds, lay, known);
+      if (kShare ? __ballot(search && !hi) != 0ull : !hi) {
+        const int tk = wave_search<OBJ, G, G, TP, kShare, T>(L, hot, search && !hi, f, ddir, wave_lds, lay, known);
         if (search && !hi) {
           taken = tk;
           if (tk < 0) {
@@ -358,13 +368,13 @@ void bfgs_kernel(const ReqDev *reqs, int nreq,
           }
         }
       }
-      if (__ballot(search && taken < 0) != 0ull) {
+      if (kShare ? __ballot(search && taken < 0) != 0ull : search && taken < 0) {
         const bool need = search && taken < 0;
-        const int tk = wave_search<OBJ, G, G, TP, double>(L, hot, need, f, ddir, wave_lds, lay, known);
+        const int tk = wave_search<OBJ, G, G, TP, kShare, double>(L, hot, need, f, ddir, wave_lds, lay, known);
         if (need) taken = tk;
       }
     } else {
-      taken = wave_search<OBJ, G, G, TP, double>(L, hot, search, f, ddir, wave_lds, lay, known);
+      taken = wave_search<OBJ, G, G, TP, kShare, double>(L, hot, search, f, ddir, wave_lds, lay, known);
     }
     wave_sync();  // every lane has read xs in the line search
     have = !whole_form<E>::value && taken >= 0;

@@ -313,7 +313,7 @@ void lbfgs_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total) {
     int taken = -1;
     if constexpr (kMixed) {
       if (__ballot(search && !hi) != 0ull) {
-        const int tk = wave_search<OBJ, G, SLOTS, TP, T>(L, hot, search && !hi, f, ddir, wave_lds, lay);
+        const int tk = wave_search<OBJ, G, SLOTS, TP, true, T>(L, hot, search && !hi, f, ddir, wave_lds, lay);
         if (search && !hi) {
           taken = tk;
           if (tk < 0) {
@@ -326,11 +326,11 @@ void lbfgs_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total) {
       }
       if (__ballot(search && taken < 0) != 0ull) {
         const bool need = search && taken < 0;
-        const int tk = wave_search<OBJ, G, SLOTS, TP, double>(L, hot, need, f, ddir, wave_lds, lay);
+        const int tk = wave_search<OBJ, G, SLOTS, TP, true, double>(L, hot, need, f, ddir, wave_lds, lay);
         if (need) taken = tk;
       }
     } else {
-      taken = wave_search<OBJ, G, SLOTS, TP, double>(L, hot, search, f, ddir, wave_lds, lay);
+      taken = wave_search<OBJ, G, SLOTS, TP, true, double>(L, hot, search, f, ddir, wave_lds, lay);
     }
     wave_sync();  // every lane has read xs and ps in the line search
 

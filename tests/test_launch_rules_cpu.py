@@ -1,0 +1,44 @@
+"""The compile-time rules of the kernels, read from the headers by the host
+compiler: which kernels share a wave's lanes in the line searches."""
+import subprocess
+
+from paper_2603_28770_amd import build as B
+from paper_2603_28770_amd import user_objectives as U
+
+OBJ = {"rosenbrock": 0, "rastrigin": 1, "ackley": 2, "styblinski_tang": 3, "goldstein_price": 4,
+       "sphere": 5, "quartic": 6}
+
+
+def _host_program(tmp_path, headers, body):
+    src = tmp_path / "rule.hip"
+    src.write_text("".join(f'#include "{h}"\n' for h in headers) + "#include <stdio.h>\n"
+                   "using namespace zeus;\nint main() {\n" + body + "\nreturn 0;\n}\n")
+    exe = tmp_path / "rule"
+    r = subprocess.run([B._hipcc(), "--offload-host-only", "-std=c++17", "-O0", "-w", "-I", B.CSRC,
+                        "-x", "hip", str(src), "-o", str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    return subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout
+
+
+def test_lanes_are_shared_where_starts_stall(tmp_path):
+    # not where the minimum is zero (no start stalls), not by a whole wave (no
+    # other group), and by two groups of 32 lanes only where it pays
+    body = "".join(f'printf("{name} {g} %d\\n", (int)kShareLanes<{o}, {g}>);\n'
+                   for name, o in OBJ.items() for g in (2, 4, 8, 16, 32, 64))
+    got = {tuple(l.split()[:2]): l.split()[2] == "1"
+           for l in _host_program(tmp_path, ["zeus_bfgs_common.h"], body).splitlines()}
+    for name in OBJ:
+        for g in (2, 4, 8, 16, 32, 64):
+            stalls = name in ("rastrigin", "ackley", "styblinski_tang", "goldstein_price")
+            want = stalls and g < 64 and not (g == 32 and name == "styblinski_tang")
+            assert got[name, str(g)] == want, (name, g)
+
+
+def test_user_code_shares_no_lanes_at_32(tmp_path):
+    # a whole-form objective tries one length per lane: 32 lanes reach past the
+    # last trial of a search by themselves
+    (tmp_path / "user.h").write_text('#include "zeus_user.h"\n' + U.ROSENBROCK)
+    body = 'printf("%d %d %d\\n", kShareLanes<kUser, 16>, kShareLanes<kUser, 32>, kShareLanes<kUser, 64>);'
+    out = _host_program(tmp_path, [str(tmp_path / "user.h"), "zeus_user_elem.h", "zeus_bfgs_common.h"],
+                        body)
+    assert out.split() == ["1", "0", "0"]
