@@ -373,8 +373,9 @@ __device__ __forceinline__ int wave_search(const GroupLanes<G> &L, const HotRegs
     do {
       const int t = base + r;
       // lanes past the last trial take a length that costs nothing, and in whole
-      // form no value either (a round of one start's lanes reaches far past it)
-      const bool tries = t < iter_ls;
+      // form no value either (a round of one start's lanes reaches far past it;
+      // one trial a round is within the loop's test)
+      const bool tries = (S == 1 && R == 1) || t < iter_ls;
       const double alpha = step_length(own + lay.al, oq.shrink, tries ? t : 0);
       // the trial's bound, formed before the terms rather than behind them
       const double bound = f + (hot.armijo_c * alpha) * ddir;
@@ -386,7 +387,7 @@ __device__ __forceinline__ int wave_search(const GroupLanes<G> &L, const HotRegs
       } else {
         ft = trial_value<OBJ, SLOTS, TP, U>(own + lay.xs, own + lay.ps, alpha, oq.d, oq.m, c, sums);
       }
-      const bool ok = open & tries & (ft <= bound);
+      const bool ok = open & (t < iter_ls) & (ft <= bound);
       const uint64_t mine = L.ballot(ok) & leaders;
       if (mine != 0ull) {
         const int first = (__ffsll((unsigned long long)mine) - 1) / TP;  // the passing trial's place

@@ -183,6 +183,10 @@ hipError_t launch_lbfgs(const Group &g, int cus);
 // Coordinate slots per L-BFGS start (power of two >= max(dim, 4); one
 // wavefront covers up to 256).
 int lbfgs_slots(int dim);
+// Whether an L-BFGS launch of `starts` starts takes the kernel with a coordinate
+// per lane (two at 128 slots), of which `room` starts are resident at once on cus
+// compute units, rather than the one with more coordinates per lane.
+bool lbfgs_spread(int objective, int precision, int slots, int64_t starts, int64_t room, int cus);
 hipError_t launch_summary(const Group &g);
 // User objectives: swarm sweep, (d <= 64) BFGS and L-BFGS launches of the
 // compiled kernels, and the dynamic LDS of a BFGS block with `lanes` lanes per

@@ -26,21 +26,42 @@ hipError_t launch_l(const Group &g, int cus) {
   return hipGetLastError();
 }
 
+// A launch with SLOTS coordinate slots per start, which two kernels can run:
+//  * dense: four coordinates per lane, so that a wave holds 256 / SLOTS starts and
+//    a sum needs one butterfly over SLOTS / 4 lanes; two at 8 slots and for the
+//    transcendental objectives, whose four-coordinate kernels pass 256
+//    registers and run one wave per SIMD (Ackley d = 50, 16,384 starts: 0.84 ms
+//    with four, 0.65 with two);
+//  * spread: a coordinate per lane (two at 128 slots), which is done sooner with
+//    one start's iteration.
+// lbfgs_spread says which.  At 128 slots the transcendental objectives' kernels
+// are the same one.
+template <int OBJ, int SLOTS, class T>
+hipError_t launch_l_slots(const Group &g, int cus) {
+  constexpr int kDense = SLOTS == 8 || OBJ == kRastrigin || OBJ == kAckley ? 2 : 4;
+  constexpr int kSpreadLanes = SLOTS < 64 ? SLOTS : 64, kSpread = SLOTS / kSpreadLanes;
+  if constexpr (kDense != kSpread) {
+    int64_t room = 0;  // starts that the spread kernel keeps resident
+    Group ask = g;
+    ask.resident = &room;
+    const hipError_t e = launch_l<OBJ, kSpreadLanes, kSpread, T>(ask, cus);
+    if (e != hipSuccess) return e;
+    // (a caller that asks for the room gets that of the largest launches' kernel)
+    if (lbfgs_spread(OBJ, g.precision, SLOTS, g.resident ? INT64_MAX / 256 : g.total_starts, room, cus))
+      return launch_l<OBJ, kSpreadLanes, kSpread, T>(g, cus);
+  }
+  return launch_l<OBJ, SLOTS / kDense, kDense, T>(g, cus);
+}
+
 template <int OBJ, class T>
 hipError_t launch_l_obj(const Group &g, int cus) {
-  // Coordinates per lane: four, so that a wave holds 256 / slots starts and a
-  // sum needs one butterfly over slots / 4 lanes; two for the transcendental
-  // objectives up to 128 slots, whose four-coordinate kernels pass 256
-  // registers and run one wave per SIMD (Ackley d = 50, 16,384 starts: 0.84 ms
-  // with four, 0.65 with two, 0.79 with one on 64 lanes).
-  constexpr int C = OBJ == kRastrigin || OBJ == kAckley ? 2 : 4;
   switch (g.g_bfgs) {  // coordinate slots per start
     case 4: return launch_l<OBJ, 4, 1, T>(g, cus);
-    case 8: return launch_l<OBJ, 4, 2, T>(g, cus);
-    case 16: return launch_l<OBJ, 16 / C, C, T>(g, cus);
-    case 32: return launch_l<OBJ, 32 / C, C, T>(g, cus);
-    case 64: return launch_l<OBJ, 64 / C, C, T>(g, cus);
-    case 128: return launch_l<OBJ, 128 / C, C, T>(g, cus);
+    case 8: return launch_l_slots<OBJ, 8, T>(g, cus);
+    case 16: return launch_l_slots<OBJ, 16, T>(g, cus);
+    case 32: return launch_l_slots<OBJ, 32, T>(g, cus);
+    case 64: return launch_l_slots<OBJ, 64, T>(g, cus);
+    case 128: return launch_l_slots<OBJ, 128, T>(g, cus);
     case 256: return launch_l<OBJ, 64, 4, T>(g, cus);
     default: return hipErrorInvalidValue;
   }
@@ -71,6 +92,32 @@ int lbfgs_slots(int dim) {
   int s = 4;
   while (s < dim) s <<= 1;
   return s;
+}
+
+// Whether a launch takes the spread kernel:
+//  * while every start has lanes of it at once, at most three wavefronts on a SIMD
+//    (at 8 slots, where the dense kernel's wave has only twice the starts, for
+//    Rosenbrock; for the others up to half a wavefront).  Spread against dense,
+//    m = 5: Rosenbrock d = 14, 1,024 starts 0.39 / 0.53 ms, d = 50, 256 starts 0.84 /
+//    1.22, 2,048 starts 1.08 / 1.25 and from there on 4,096 starts 1.60 / 1.30, 16,384
+//    starts 5.09 / 2.95, d = 7, 16,384 starts 0.48 / 0.53; Styblinski-Tang d = 30,
+//    4,096 starts 0.192 / 0.210, 8,192 starts 0.250 / 0.247; Rastrigin d = 6, 4,096
+//    starts 0.175 / 0.179, 8,192 starts 0.202 / 0.195;
+//  * in mixed precision, where many starts stall after the change to FP64 and one
+//    of them sets the end of the launch by itself, always for the objectives
+//    that have such starts: Styblinski-Tang d = 30, 16,384 starts 4.9 / 8.6 ms,
+//    Rastrigin d = 45, 30,000 starts 5.6 / 7.9, Ackley d = 10, 30,000 starts 7.8 /
+//    11.8.  (Ackley from d = 17 on loses more without stalls than it gains with
+//    them: d = 30, 30,000 starts 0.71 / 0.60; and so does Styblinski-Tang d = 6 0.42 /
+//    0.34.)
+bool lbfgs_spread(int objective, int precision, int slots, int64_t starts, int64_t room, int cus) {
+  const int64_t lanes = (int64_t)starts * (slots < 64 ? slots : 64);
+  const int64_t per_wave = 4 * 64 * (int64_t)cus;  // lanes of one wavefront per SIMD
+  if (slots == 8 && objective != kRosenbrock) return 2 * lanes <= per_wave;
+  if (starts <= room && lanes <= 3 * per_wave) return true;
+  if (precision != ZEUS_MIXED) return false;
+  return objective == kRastrigin || objective == kStyblinskiTang ||
+         (objective == kAckley && slots == 16);
 }
 
 hipError_t launch_lbfgs(const Group &g, int cus) {

@@ -67,13 +67,21 @@ void lbfgs_kernel(const ReqDev *reqs, int nreq, BatchDev *hdr, int64_t total) {
   StartCounts *cnt;  // the start's pair skips and direction resets (lane 0)
   ReqHot *qh;
   constexpr SearchLayout lay = lbfgs_search_layout(SLOTS);
-  // A trial takes all the group's lanes, a lane its own coordinates' terms: at
-  // one to two trials per iteration more of them a round are mostly wasted
-  // (two a round: d = 200 26.5 ms against 22.3, d = 100 7.2 against 6.4), and
-  // wave_search gives a search that goes on the other groups' lanes.  Groups
-  // of four lanes take two or four, for the starts that stall at small d
-  // (Ackley d = 4, 8,192 starts: 13.4 ms with one, 7.7 with four).
-  constexpr int TP = whole_form<Elem<OBJ>>::value || SLOTS == 4 ? 1 : G == 4 ? 2 : G;
+  // Lanes per trial.  With several coordinates per lane a trial takes all the
+  // group's lanes, a lane its own coordinates' terms: at one to two trials per
+  // iteration more of them a round are mostly wasted (two a round: d = 200 26.5 ms
+  // against 22.3, d = 100 7.2 against 6.4), and wave_search gives a search that
+  // goes on the other groups' lanes.  Groups of four lanes take two or four, for
+  // the starts that stall at small d (Ackley d = 4, 8,192 starts: 13.4 ms with one,
+  // 7.7 with four).  With a coordinate per lane a round has four trials as in
+  // the BFGS kernels, on 64 lanes two (Styblinski-Tang d = 120, 1,024 starts that
+  // stall, 300 iterations: 2.2 ms with one, 1.4 with two).
+  constexpr bool kCostly = OBJ == kRastrigin || OBJ == kAckley;
+  constexpr int TP = whole_form<Elem<OBJ>>::value || SLOTS == 4      ? 1
+                     : G == 64 && CPL <= 2 && !(CPL == 2 && kCostly) ? 32
+                     : CPL == 1                                      ? G / 4
+                     : G == 4                                        ? 2
+                                                                     : G;
   double *wave_lds = smem + (size_t)((threadIdx.x >> 6) * S) * lay.stride;
   {
     double *base = wave_lds + L.grp * lay.stride;

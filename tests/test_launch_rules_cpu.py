@@ -1,5 +1,6 @@
-"""The compile-time rules of the kernels, read from the headers by the host
-compiler: which kernels share a wave's lanes in the line searches."""
+"""The rules that choose kernels: the compile-time ones read from the headers by
+a host program, the library's own called from one."""
+import os
 import subprocess
 
 from paper_2603_28770_amd import build as B
@@ -42,3 +43,33 @@ def test_user_code_shares_no_lanes_at_32(tmp_path):
     out = _host_program(tmp_path, [str(tmp_path / "user.h"), "zeus_user_elem.h", "zeus_bfgs_common.h"],
                         body)
     assert out.split() == ["1", "0", "0"]
+
+
+def test_lbfgs_kernel_of_a_launch(tmp_path):
+    # few starts, and in mixed precision the objectives whose starts stall, take
+    # a coordinate per lane (the library's own rule, called from a small program)
+    from paper_2603_28770_amd import zeus as Z
+    cases = [(o, p, s, n) for o in OBJ.values() for p in (0, 1) for s in (8, 16, 32, 64, 128)
+             for n in (1, 256, 1024, 4096, 4097, 65536, 2**40)]
+    (tmp_path / "rule.cpp").write_text(
+        '#include "zeus_internal.h"\n#include <stdio.h>\nint main() {\nint o, p, s; long n;\n'
+        'while (scanf("%d %d %d %ld", &o, &p, &s, &n) == 4)\n'
+        '  printf("%d\\n", (int)zeus::lbfgs_spread(o, p, s, n, 12288 * 16 / s, 256));\nreturn 0; }\n')
+    exe = tmp_path / "rule"
+    r = subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-w", "-I", B.CSRC, "-I", "/opt/rocm/include",
+                        str(tmp_path / "rule.cpp"), Z.LIB_PATH, f"-Wl,-rpath,{os.path.dirname(Z.LIB_PATH)}",
+                        "-L/opt/rocm/lib", "-Wl,-rpath,/opt/rocm/lib", "-lamdhip64", "-o", str(exe)],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-3000:]
+    out = subprocess.run([str(exe)], input="".join("%d %d %d %d\n" % c for c in cases),
+                         capture_output=True, text=True, check=True).stdout.split()
+    assert len(out) == len(cases)
+    for (o, p, s, n), got in zip(cases, out):
+        lanes = n * min(s, 64)
+        if s == 8 and o != OBJ["rosenbrock"]:
+            want = lanes <= 32768  # half a wavefront on each SIMD of 256 units
+        else:
+            want = n <= 12288 * 16 // s and lanes <= 3 * 65536
+            if p == 1:
+                want = want or o in (OBJ["rastrigin"], OBJ["styblinski_tang"]) or (o == OBJ["ackley"] and s == 16)
+        assert (got == "1") == want, (o, p, s, n)
