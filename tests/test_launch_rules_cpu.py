@@ -45,24 +45,31 @@ def test_user_code_shares_no_lanes_at_32(tmp_path):
     assert out.split() == ["1", "0", "0"]
 
 
-def test_lbfgs_kernel_of_a_launch(tmp_path):
-    # few starts, and in mixed precision the objectives whose starts stall, take
-    # a coordinate per lane (the library's own rule, called from a small program)
+def _library_program(tmp_path, code, stdin):
+    """Output lines of a program that calls the library's own rules."""
     from paper_2603_28770_amd import zeus as Z
-    cases = [(o, p, s, n) for o in OBJ.values() for p in (0, 1) for s in (8, 16, 32, 64, 128)
-             for n in (1, 256, 1024, 4096, 4097, 65536, 2**40)]
-    (tmp_path / "rule.cpp").write_text(
-        '#include "zeus_internal.h"\n#include <stdio.h>\nint main() {\nint o, p, s; long n;\n'
-        'while (scanf("%d %d %d %ld", &o, &p, &s, &n) == 4)\n'
-        '  printf("%d\\n", (int)zeus::lbfgs_spread(o, p, s, n, 12288 * 16 / s, 256));\nreturn 0; }\n')
+    (tmp_path / "rule.cpp").write_text('#include "zeus_internal.h"\n#include <stdio.h>\n'
+                                       "int main() {\n" + code + "\nreturn 0; }\n")
     exe = tmp_path / "rule"
-    r = subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-w", "-I", B.CSRC, "-I", "/opt/rocm/include",
-                        str(tmp_path / "rule.cpp"), Z.LIB_PATH, f"-Wl,-rpath,{os.path.dirname(Z.LIB_PATH)}",
-                        "-L/opt/rocm/lib", "-Wl,-rpath,/opt/rocm/lib", "-lamdhip64", "-o", str(exe)],
+    r = subprocess.run(["g++", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-w", "-I", B.CSRC, "-I",
+                        "/opt/rocm/include", str(tmp_path / "rule.cpp"), Z.LIB_PATH,
+                        f"-Wl,-rpath,{os.path.dirname(Z.LIB_PATH)}", "-L/opt/rocm/lib",
+                        "-Wl,-rpath,/opt/rocm/lib", "-lamdhip64", "-o", str(exe)],
                        capture_output=True, text=True)
     assert r.returncode == 0, r.stderr[-3000:]
-    out = subprocess.run([str(exe)], input="".join("%d %d %d %d\n" % c for c in cases),
-                         capture_output=True, text=True, check=True).stdout.split()
+    return subprocess.run([str(exe)], input=stdin, capture_output=True, text=True,
+                          check=True).stdout.split()
+
+
+def test_lbfgs_kernel_of_a_launch(tmp_path):
+    # few starts, and in mixed precision the objectives whose starts stall, take
+    # a coordinate per lane
+    cases = [(o, p, s, n) for o in OBJ.values() for p in (0, 1) for s in (8, 16, 32, 64, 128)
+             for n in (1, 256, 1024, 4096, 4097, 65536, 2**40)]
+    out = _library_program(
+        tmp_path, 'int o, p, s; long n;\nwhile (scanf("%d %d %d %ld", &o, &p, &s, &n) == 4)\n'
+        '  printf("%d\\n", (int)zeus::lbfgs_spread(o, p, s, n, 12288 * 16 / s, 256));',
+        "".join("%d %d %d %d\n" % c for c in cases))
     assert len(out) == len(cases)
     for (o, p, s, n), got in zip(cases, out):
         lanes = n * min(s, 64)
@@ -73,3 +80,16 @@ def test_lbfgs_kernel_of_a_launch(tmp_path):
             if p == 1:
                 want = want or o in (OBJ["rastrigin"], OBJ["styblinski_tang"]) or (o == OBJ["ackley"] and s == 16)
         assert (got == "1") == want, (o, p, s, n)
+
+
+def test_three_wavefront_blocks(tmp_path):
+    # with the transcendental terms only launches of more than eight starts per
+    # unit (they are slower one by one, and more of them fit)
+    cases = [(o, n) for o in OBJ.values() for n in (1, 512, 2048, 2049, 65536)]
+    out = _library_program(
+        tmp_path, 'int o; long n;\nwhile (scanf("%d %ld", &o, &n) == 2)\n'
+        '  printf("%d\\n", (int)zeus::tile_three(o, n, 256));',
+        "".join("%d %d\n" % c for c in cases))
+    for (o, n), got in zip(cases, out):
+        costly = o in (OBJ["rastrigin"], OBJ["ackley"])
+        assert (got == "1") == (not costly or n > 2048), (o, n)
