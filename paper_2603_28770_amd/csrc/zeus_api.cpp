@@ -269,6 +269,9 @@ int max_dim(const std::vector<Planned> &reqs) {
 size_t hslot_bytes(int g_bfgs, int64_t total_starts, int dmax) {
   return g_bfgs == zeus::kWideLanes ? align_up(zeus::wide_hslot_bytes(total_starts, dmax)) : 0;
 }
+size_t hslot_reserved(int g_bfgs, int64_t total_starts, int dmax) {
+  return g_bfgs == zeus::kWideLanes ? align_up(zeus::wide_reserved_bytes(total_starts, dmax)) : 0;
+}
 
 // Method (0 BFGS, 1 L-BFGS) and lanes / coordinate slots per start of a problem.
 int method_of(const zeus_problem &p) { return p.lbfgs_m > 0 ? 1 : 0; }
@@ -322,7 +325,6 @@ zeus_err build_group(const std::vector<Planned> &reqs, void *hdr_table, void *hs
   g.stream = stream;
   g.hslots = static_cast<double *>(hslots);
   g.wide_slots = 0;
-  g.wide_cs = 0;
   g.wide_slot_doubles = 0;
   g.user = nullptr;
   g.early_stop = false;
@@ -372,8 +374,7 @@ zeus_err build_group(const std::vector<Planned> &reqs, void *hdr_table, void *hs
   if (g.method == 0 && g.g_bfgs == zeus::kWideLanes) {
     const int dmax = max_dim(reqs);
     g.wide_slots = zeus::wide_slots(g.total_starts);
-    g.wide_cs = zeus::wide_cs(dmax);
-    g.wide_slot_doubles = (int64_t)dmax * g.wide_cs;
+    g.wide_slot_doubles = zeus::wide_slot_doubles(dmax);
     if (!hslots && need_hslots) return fail(ZEUS_EINVAL, "wide problem without H slots");
   }
   return ZEUS_OK;
@@ -571,7 +572,9 @@ struct BatchPlan {
   size_t res_total = 0, ws_total = 0;
 };
 
-BatchPlan plan_batch(const zeus_problem *problems, const zeus_result *outs, int32_t n) {
+// reserved: H slots as the public interface counts them (a workspace of the
+// caller's), otherwise what the kernels use.
+BatchPlan plan_batch(const zeus_problem *problems, const zeus_result *outs, int32_t n, bool reserved) {
   BatchPlan b;
   for (int32_t r = 0; r < n; ++r) {
     const GroupKey k = key_of(problems[r]);
@@ -601,7 +604,8 @@ BatchPlan plan_batch(const zeus_problem *problems, const zeus_result *outs, int3
       starts += problems[r].n_starts;
       dmax = problems[r].dim > dmax ? problems[r].dim : dmax;
     }
-    const size_t hb = hslot_bytes(b.order[gi].method ? 0 : b.order[gi].g_bfgs, starts, dmax);
+    const int lanes = b.order[gi].method ? 0 : b.order[gi].g_bfgs;
+    const size_t hb = reserved ? hslot_reserved(lanes, starts, dmax) : hslot_bytes(lanes, starts, dmax);
     b.h_off[gi] = hb ? b.ws_total : SIZE_MAX;
     b.ws_total += hb;
   }
@@ -857,7 +861,7 @@ zeus_err zeus_workspace_bytes(const zeus_problem *problem, size_t *bytes) {
   zeus_err e = check_problem(problem);
   if (e != ZEUS_OK) return e;
   *bytes = kHdrBytes + table_bytes(1) + request_ws_bytes(*problem) +
-           hslot_bytes(hslot_lanes(*problem), problem->n_starts, problem->dim);
+           hslot_reserved(hslot_lanes(*problem), problem->n_starts, problem->dim);
   return ZEUS_OK;
 }
 
@@ -1023,7 +1027,7 @@ zeus_err minimize_batch(zeus_context *ctx, const zeus_problem *problems, int32_t
     if (e == ZEUS_OK) e = check_result(&outs[r], &problems[r]);
     if (e != ZEUS_OK) return fail(e, "request " + std::to_string(r) + ": " + g_last_error);
   }
-  const BatchPlan plan = plan_batch(problems, outs, n);
+  const BatchPlan plan = plan_batch(problems, outs, n, false);
   DeviceGuard dg(ctx->device);
   if (dg.err != hipSuccess) return hip_fail(dg.err, "hipSetDevice");
   std::lock_guard<std::mutex> lk(ctx->mu);
@@ -1129,7 +1133,7 @@ zeus_err zeus_plan_workspace_bytes(const zeus_problem *problems, int32_t n, size
     zeus_err e = check_problem(&problems[r]);
     if (e != ZEUS_OK) return fail(e, "request " + std::to_string(r) + ": " + g_last_error);
   }
-  *bytes = plan_batch(problems, none.data(), n).ws_total;
+  *bytes = plan_batch(problems, none.data(), n, true).ws_total;
   return ZEUS_OK;
 }
 
@@ -1155,7 +1159,7 @@ zeus_err zeus_plan_create(zeus_context *ctx, const zeus_problem *problems, int32
       r.trace = nullptr;
       r.trace_len = 0;
     }
-  const BatchPlan b = plan_batch(problems, res.data(), n);
+  const BatchPlan b = plan_batch(problems, res.data(), n, true);
   if (!workspace || workspace_bytes < b.ws_total)
     return fail(ZEUS_EINVAL, "workspace missing or smaller than zeus_plan_workspace_bytes()");
   if (reinterpret_cast<uintptr_t>(workspace) % kAlign != 0)

@@ -265,10 +265,24 @@ int wide_slots(int64_t total_starts) {
   return (int)(total_starts < kWideMaxSlots ? total_starts : kWideMaxSlots);
 }
 
-int wide_cs(int dmax) { return (dmax + 63) / 64 * 64; }
+// A matrix, rows rounded up to 64 columns.
+static int64_t wide_matrix_doubles(int dmax) { return (int64_t)dmax * ((dmax + 63) / 64 * 64); }
+
+// (a matrix that is smaller than a slot belongs to a dimension that has no strip
+// in the slot)
+static_assert((160 + 1) * 192 >= kWideSlotDoubles, "from 161 dimensions on a slot holds the strips");
+int64_t wide_slot_doubles(int dmax) {
+  const int64_t m = wide_matrix_doubles(dmax);
+  return m < kWideSlotDoubles ? m : kWideSlotDoubles;
+}
 
 size_t wide_hslot_bytes(int64_t total_starts, int dmax) {
-  return sizeof(double) * (size_t)wide_slots(total_starts) * (size_t)dmax * (size_t)wide_cs(dmax);
+  return sizeof(double) * (size_t)wide_slots(total_starts) * (size_t)wide_slot_doubles(dmax);
+}
+
+size_t wide_reserved_bytes(int64_t total_starts, int dmax) {
+  return sizeof(double) * (size_t)(total_starts < 2048 ? total_starts : 2048) *
+         (size_t)wide_matrix_doubles(dmax);
 }
 
 hipError_t launch_es_finish(const Group &g) {

@@ -48,6 +48,8 @@ constexpr int kWVec = tile_vec_len(256);  // doubles of a padded operand vector 
 constexpr int kStripLds = 2;              // strips of a wavefront in LDS (the other two in the slot)
 // doubles of a wavefront's strips in the slot
 constexpr int kSlotWave = (4 - kStripLds) * 16 * 64;
+static_assert(kWW * kSlotWave == kWideSlotDoubles, "the slot holds the strips that are not in LDS");
+static_assert(128 + 16 * kStripLds == 160, "up to dimension 160 no strip is in the slot");
 
 struct alignas(16) Pair {
   double a, b;  // two consecutive columns

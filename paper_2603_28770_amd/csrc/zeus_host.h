@@ -75,6 +75,8 @@ struct Planned {
 int max_dim(const std::vector<Planned> &reqs);
 // Device bytes of the H slots a group needs (0 unless its problems are wide).
 size_t hslot_bytes(int g_bfgs, int64_t total_starts, int dmax);
+// The same as the public interface counts them.
+size_t hslot_reserved(int g_bfgs, int64_t total_starts, int dmax);
 // Method (0 BFGS, 1 L-BFGS) and lanes / coordinate slots per start.
 int method_of(const zeus_problem &p);
 int lanes_of(const zeus_problem &p);

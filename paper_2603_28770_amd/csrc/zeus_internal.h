@@ -29,8 +29,13 @@ constexpr int kTile3Dim = 96;
 constexpr int kTileBlockDim = 128;
 constexpr int kHybridDim = 208;
 constexpr int kWideLanes = 256;
-// Most H slots (resident wide blocks) a launch group uses.
-constexpr int kWideMaxSlots = 2048;
+// Most H slots a launch group uses: its resident wide blocks, of which each fills
+// one of the 256 compute units.
+constexpr int kWideMaxSlots = 256;
+// Doubles of a slot that the wide block reads and writes: two strips of 16
+// columns for each of its eight wavefronts' 64 rows (none up to dimension 160,
+// whose strips are all in LDS).
+constexpr int kWideSlotDoubles = 8 * 2 * 16 * 64;
 // Most (s, y) pairs an L-BFGS start keeps (in registers).
 constexpr int kLbfgsMaxHistory = 8;
 constexpr int kPsoBlock = 256;
@@ -155,18 +160,21 @@ struct Group {
   // wide problems (g_bfgs == kWideLanes): the blocks' H slots
   double *hslots;            // [wide_slots][wide_slot_doubles]
   int wide_slots;
-  int wide_cs;               // column stride of a slot (max dim rounded up to 64)
-  int64_t wide_slot_doubles; // max dim * wide_cs
+  int64_t wide_slot_doubles; // from one slot to the next
   const UserKernels *user;   // objective == kUser: its compiled kernels
   bool early_stop;           // some request has required_converged > 0
   int64_t *resident;         // non-null: the BFGS launcher only stores here how many
                              // starts its kernel keeps resident at once (no launch)
 };
 
-// H slots of a wide launch group whose largest dimension is dmax.
+// H slots of a wide launch group whose largest dimension is dmax: their number,
+// the doubles of one and the bytes of all.
 int wide_slots(int64_t total_starts);
-int wide_cs(int dmax);
+int64_t wide_slot_doubles(int dmax);
 size_t wide_hslot_bytes(int64_t total_starts, int dmax);
+// Bytes that the sizes of the public interface count for them (zeus.h: a slot of
+// the whole matrix per start, at most 2048); never less than wide_hslot_bytes.
+size_t wide_reserved_bytes(int64_t total_starts, int dmax);
 
 // Kernel launchers (return the first HIP error, hipSuccess otherwise).
 hipError_t launch_ws_init(const Group &g);

@@ -119,8 +119,6 @@ size_t request_bytes(const zeus_problem &pb, const zeus_result &out) {
          table_bytes(1);
 }
 
-// Bytes of one H slot of a wide problem of dimension d.
-size_t hslot_one(int d) { return sizeof(double) * (size_t)d * (size_t)zeus::wide_cs(d); }
 
 class Device {
  public:
@@ -207,7 +205,7 @@ class HipDevice : public Device {
     zeus::Group &g = st.run.g;
     if (g.method == 0 && g.g_bfgs == zeus::kWideLanes) {
       // as many H slots (one per resident block) as the buffer holds
-      const int64_t fit = (int64_t)(hs_bytes / hslot_one(max_dim(planned)));
+      const int64_t fit = (int64_t)(hs_bytes / (sizeof(double) * (size_t)g.wide_slot_doubles));
       if (fit < 1) return fail(ZEUS_ENOMEM, "step buffer holds no H slot");
       if (g.wide_slots > fit) g.wide_slots = (int)fit;
     }
@@ -628,7 +626,7 @@ zeus_err zeus_server_submit(zeus_server *srv, const zeus_problem *problem,
                                  " bytes of device memory, more than the server's budget for "
                                  "requests (" + std::to_string(srv->budget) + ")");
   if (hslot_lanes(r->pb) == zeus::kWideLanes &&
-      srv->step_bytes < step_table_bytes(1) + hslot_one(r->pb.dim))
+      srv->step_bytes < step_table_bytes(1) + zeus::wide_reserved_bytes(1, r->pb.dim))
     return fail(ZEUS_ENOMEM, "budget too small for one inverse-Hessian slot of this dimension");
   r->times.t_submit_ns = now_ns();
   std::lock_guard<std::mutex> lk(srv->mu);
