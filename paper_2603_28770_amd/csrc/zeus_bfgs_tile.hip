@@ -27,7 +27,7 @@ hipError_t launch_tile_nb(const Group &g, int cus) {
 
 template <int OBJ, class T>
 hipError_t launch_tile_t(const Group &g, int cus) {
-  if (g.g_bfgs == kTile3Dim && (g.resident || tile_three(OBJ, g.total_starts, cus)))
+  if (g.g_bfgs == kTile3Dim && (g.resident || tile_three(OBJ, g.precision, g.total_starts, cus)))
     return launch_tile_nb<OBJ, T, 6>(g, cus);
   return launch_tile_nb<OBJ, T, 8>(g, cus);
 }
@@ -53,14 +53,16 @@ hipError_t launch_tile_prec(const Group &g, int cus) {
 // it spills 57 to 74 registers, and a search has three trials a round instead
 // of four: an iteration takes a fifth longer and a search that fails seven rounds
 // instead of five.  Its four blocks on a CU against two make up for it from about
-// twelve starts per CU on; the line lies where no start stalls (with stalls up to
-// 4,096 starts are even or slower).  Three against four wavefronts, d = 66 .. 96,
-// ms: Ackley, 256 starts 0.26 / 0.20, 1,024 starts 0.37 / 0.36, 2,048 starts 0.55 / 0.56,
-// 4,096 starts 0.89 / 0.96, stalled 1,024 starts 4.7 / 3.3, stalled 4,096 starts 7.1 /
-// 7.0; Rastrigin in mixed precision 512 starts 0.71 / 0.51, 2,048 starts 1.24 / 1.13,
-// 4,096 starts 1.85 / 1.83, 8,192 starts 3.23 / 3.38.
-bool tile_three(int objective, int64_t starts, int cus) {
-  return !(objective == kRastrigin || objective == kAckley) || starts > 8 * (int64_t)cus;
+// eight starts per CU on, in mixed precision sixteen; the lines lie where no start
+// stalls (a launch that ends with one stalled start is slower up to many more:
+// Rastrigin d = 72, 4,094 starts 7.7 / 6.0).  Three against four wavefronts, d = 66 ..
+// 96, ms: Ackley, 256 starts 0.26 / 0.20, 1,024 starts 0.37 / 0.36, 2,048 starts 0.55 /
+// 0.56, 4,096 starts 0.89 / 0.96; Rastrigin 4,096 starts 1.84 / 1.99; in mixed
+// precision Rastrigin 512 starts 0.71 / 0.51, 4,096 starts 2.07 / 1.94, 8,192 starts
+// 2.82 / 2.90, Ackley 4,096 starts 1.02 / 0.98, 8,192 starts 1.69 / 1.73.
+bool tile_three(int objective, int precision, int64_t starts, int cus) {
+  if (objective != kRastrigin && objective != kAckley) return true;
+  return starts > (precision == ZEUS_MIXED ? 16 : 8) * (int64_t)cus;
 }
 
 hipError_t launch_bfgs_tile(const Group &g, int cus) {

@@ -188,7 +188,7 @@ hipError_t launch_bfgs_wide(const Group &g, int cus);
 hipError_t launch_bfgs_tile(const Group &g, int cus);
 // Whether a launch of `starts` starts of dimension <= kTile3Dim takes the block of
 // three wavefronts rather than four.
-bool tile_three(int objective, int64_t starts, int cus);
+bool tile_three(int objective, int precision, int64_t starts, int cus);
 hipError_t launch_bfgs_hybrid(const Group &g, int cus);
 hipError_t launch_lbfgs(const Group &g, int cus);
 // Coordinate slots per L-BFGS start (power of two >= max(dim, 4); one

@@ -1,6 +1,6 @@
 """Objectives with transcendental terms take the block of three wavefronts only
 in large launches, the one of four in small ones: at the edges of the column
-blocks, the same bits from both as the oracle.  (One unit makes ten starts a
+blocks, the same bits from both as the oracle.  (One unit makes 18 starts a
 large launch.)  And without forcing anything a small launch takes as long as
 with four wavefronts forced."""
 import time
@@ -35,7 +35,7 @@ def ctx(Z):
 @pytest.mark.parametrize("objective", ["rastrigin", "ackley"])
 def test_both_blocks(Z, ctx, oracle_mod, monkeypatch, objective, d):
     lo, hi = W.BOXES[objective]
-    p = W.problem(objective=objective, dim=d, n=10, lower=lo, upper=hi, iter_pso=1, iter_bfgs=40, seed=d)
+    p = W.problem(objective=objective, dim=d, n=18, lower=lo, upper=hi, iter_pso=1, iter_bfgs=40, seed=d)
     print(f"\n[tile] {objective} d={d}", flush=True)
     four = Z.zeus_minimize(ctx, p)
     mixed_four = Z.zeus_minimize(ctx, dict(p, precision="mixed"))

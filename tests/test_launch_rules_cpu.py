@@ -84,15 +84,17 @@ def test_lbfgs_kernel_of_a_launch(tmp_path):
 
 def test_three_wavefront_blocks(tmp_path):
     # with the transcendental terms only launches of more than eight starts per
-    # unit (they are slower one by one, and more of them fit)
-    cases = [(o, n) for o in OBJ.values() for n in (1, 512, 2048, 2049, 65536)]
+    # unit, in mixed precision sixteen (they are slower one by one, and more of
+    # them fit)
+    cases = [(o, p, n) for o in OBJ.values() for p in (0, 1) for n in (1, 512, 2048, 2049, 4096, 4097, 65536)]
     out = _library_program(
-        tmp_path, 'int o; long n;\nwhile (scanf("%d %ld", &o, &n) == 2)\n'
-        '  printf("%d\\n", (int)zeus::tile_three(o, n, 256));',
-        "".join("%d %d\n" % c for c in cases))
-    for (o, n), got in zip(cases, out):
+        tmp_path, 'int o, p; long n;\nwhile (scanf("%d %d %ld", &o, &p, &n) == 3)\n'
+        '  printf("%d\\n", (int)zeus::tile_three(o, p, n, 256));',
+        "".join("%d %d %d\n" % c for c in cases))
+    assert len(out) == len(cases)
+    for (o, p, n), got in zip(cases, out):
         costly = o in (OBJ["rastrigin"], OBJ["ackley"])
-        assert (got == "1") == (not costly or n > 2048), (o, n)
+        assert (got == "1") == (not costly or n > (4096 if p else 2048)), (o, p, n)
 
 
 def test_wide_slots(tmp_path):
