@@ -168,9 +168,10 @@ struct Group {
 };
 
 // H slots of a wide launch group whose largest dimension is dmax: their number,
-// the doubles of one and the bytes of all.
+// the doubles from one to the next, the fewest that may be, and the bytes of all.
 int wide_slots(int64_t total_starts);
 int64_t wide_slot_doubles(int dmax);
+int64_t wide_slot_least(int dmax);
 size_t wide_hslot_bytes(int64_t total_starts, int dmax);
 // Bytes that the sizes of the public interface count for them (zeus.h: a slot of
 // the whole matrix per start, at most 2048); never less than wide_hslot_bytes.

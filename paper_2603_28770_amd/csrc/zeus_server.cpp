@@ -205,7 +205,12 @@ class HipDevice : public Device {
     zeus::Group &g = st.run.g;
     if (g.method == 0 && g.g_bfgs == zeus::kWideLanes) {
       // as many H slots (one per resident block) as the buffer holds
-      const int64_t fit = (int64_t)(hs_bytes / (sizeof(double) * (size_t)g.wide_slot_doubles));
+      // (end to end if it does not hold them a matrix apart)
+      int64_t fit = (int64_t)(hs_bytes / (sizeof(double) * (size_t)g.wide_slot_doubles));
+      if (fit < g.wide_slots) {
+        g.wide_slot_doubles = zeus::wide_slot_least(max_dim(planned));
+        fit = (int64_t)(hs_bytes / (sizeof(double) * (size_t)g.wide_slot_doubles));
+      }
       if (fit < 1) return fail(ZEUS_ENOMEM, "step buffer holds no H slot");
       if (g.wide_slots > fit) g.wide_slots = (int)fit;
     }

@@ -98,18 +98,20 @@ def test_three_wavefront_blocks(tmp_path):
 
 
 def test_wide_slots(tmp_path):
-    # slots hold the strips that the wide block keeps there (its second tile's
-    # columns from 160 on, two strips of 16 columns by 512 rows), no launch needs
-    # more than the public sizes count, and a server step of 64 MiB has a slot for
-    # every unit
+    # the least slot holds the strips that the wide block keeps there (its second
+    # tile's columns from 160 on, two strips of 16 columns by 512 rows), no launch
+    # needs more than the public sizes count, and a server step of 64 MiB has a
+    # slot for every unit
     code = ('for (int d = 1; d <= 256; ++d)\n  for (long n : {1l, 300l, 5000l})\n'
-            '    printf("%d %ld %d %ld %zu %zu\\n", d, n, zeus::wide_slots(n), (long)zeus::wide_slot_doubles(d),\n'
+            '    printf("%d %ld %d %ld %ld %zu %zu\\n", d, n, zeus::wide_slots(n),\n'
+            '           (long)zeus::wide_slot_doubles(d), (long)zeus::wide_slot_least(d),\n'
             '           zeus::wide_hslot_bytes(n, d), zeus::wide_reserved_bytes(n, d));')
     vals = [int(v) for v in _library_program(tmp_path, code, "")]
-    rows = [vals[i:i + 6] for i in range(0, len(vals), 6)]
+    rows = [vals[i:i + 7] for i in range(0, len(vals), 7)]
     assert len(rows) == 256 * 3
-    for d, n, slots, one, need, reserved in rows:
-        assert slots == min(n, 256) and need == 8 * slots * one and one % 2 == 0
+    for d, n, slots, apart, least, need, reserved in rows:
+        assert slots == min(n, 256) and least <= apart and need == 8 * slots * apart
+        assert apart % 2 == 0 and least % 2 == 0
         assert need <= reserved == 8 * min(n, 2048) * d * ((d + 63) // 64 * 64)
         if d > 160:
-            assert one == 16 * 1024 and (64 << 20) // (8 * one) >= 256
+            assert least == 16 * 1024 and (64 << 20) // (8 * least) >= 256
