@@ -5,7 +5,8 @@
 For every objective, precision and probe dimension it times each candidate
 tiling of the BFGS phase:
   * one group of G lanes per start, G a power of two from max(4, next_pow2(d))
-    up to 64 (H in registers, 64/G starts per wavefront);
+    up to 64 (H in registers, 64/G starts per wavefront), 64 lanes with the
+    cut tile where a table entry of 64 would run it;
   * one block per start with a part of H in a device-memory slot.
 Every tiling computes the same pairwise sums, so the tuner also checks that
 all candidates return bit-identical results.  The fastest tiling of each probe
@@ -31,6 +32,8 @@ OBJECTIVES = {"rosenbrock": 0, "rastrigin": 1, "ackley": 2, "styblinski_tang": 3
 PRECISIONS = {"fp64": 0, "mixed": 1}
 DIMS = [2, 3, 4, 6, 8, 12, 16, 24, 32, 40, 48, 56, 64]
 WIDE = 256
+# Where the library runs 64 lanes with the cut tile (tiling 52)
+CUT_DIM, CUT_OBJECTIVES = 52, ("rosenbrock", "styblinski_tang")
 
 
 def candidates(d):
@@ -44,6 +47,11 @@ def candidates(d):
     return out + [WIDE]
 
 
+def forced_tiling(obj, d, lanes):
+    """The tiling that a table entry of `lanes` runs."""
+    return CUT_DIM if lanes == 64 and d <= CUT_DIM and obj in CUT_OBJECTIVES else lanes
+
+
 def probe_problem(obj, prec, d, quick):
     lo, hi = W.BOXES[obj]
     # about 2^22 coordinate-starts, at least 1024 starts
@@ -53,7 +61,7 @@ def probe_problem(obj, prec, d, quick):
 
 
 def time_tiling(Z, ctx, torch, p, lanes, reps):
-    os.environ["ZEUS_TILE_LANES"] = str(lanes)
+    os.environ["ZEUS_TILE_LANES"] = str(forced_tiling(p["objective"], p["dim"], lanes))
     try:
         ds = Z.DeviceSolve(p)
         stream = torch.cuda.Stream()

@@ -115,3 +115,17 @@ def test_wide_slots(tmp_path):
         assert need <= reserved == 8 * min(n, 2048) * d * ((d + 63) // 64 * 64)
         if d > 160:
             assert least == 16 * 1024 and (64 << 20) // (8 * least) >= 256
+
+
+def test_autotuner_times_what_a_table_entry_runs(tmp_path):
+    # an entry of 64 lanes runs the cut tile where there is one (the library's own
+    # choice for every objective and dimension that the table gives 64 lanes)
+    from paper_2603_28770_amd import autotune as A
+    cases = [(name, prec, d) for name in A.OBJECTIVES for prec in (0, 1) for d in range(33, 65)]
+    out = _library_program(
+        tmp_path, 'int o, p, d;\nwhile (scanf("%d %d %d", &o, &p, &d) == 3)\n'
+        '  printf("%d\\n", zeus::group_lanes(o, p, d));',
+        "".join("%d %d %d\n" % (A.OBJECTIVES[n], p, d) for n, p, d in cases))
+    for (name, prec, d), got in zip(cases, out):
+        assert int(got) == A.forced_tiling(name, d, 64), (name, prec, d)
+    assert A.forced_tiling("rosenbrock", 40, 256) == 256 and A.forced_tiling("rosenbrock", 16, 16) == 16
