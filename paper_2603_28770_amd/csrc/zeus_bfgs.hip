@@ -181,8 +181,9 @@ hipError_t launch_prec(const Group &g, int64_t want, int cus) {
 
 // Tiling: lanes per start (2..64, a power of two >= dim: one group per start, H
 // in registers), kCutDim (64 lanes with the cut tile, dim <= 52), kTile3Dim
-// (one block of three wavefronts per start, H in their registers, dim <= 96;
-// not for user objectives, which have a lane per coordinate of 128),
+// (one block of three wavefronts per start, H in their registers, dim <= 96, or of
+// four where tile_three says so; not for user objectives, which have a lane per
+// coordinate of 128),
 // kTileBlockDim (four wavefronts, dim <= 128), kHybridDim (one block of eight
 // wavefronts per start, H in their registers and LDS, dim <= 208) or kWideLanes
 // (one block of eight wavefronts per start, H in registers, LDS and a slot in
@@ -190,7 +191,8 @@ hipError_t launch_prec(const Group &g, int64_t want, int cus) {
 // Every tiling computes the same pairwise trees, so results do not depend on
 // it; only speed does.  The rules come from the autotuner's table; a start
 // no rule covers gets the smallest power of two >= max(dim, 4), or above 64
-// dimensions the first block that holds it.  Where the table says 64 lanes the
+// dimensions the first block that holds it.  (The table's times are of kernels
+// without shared line searches and the cut tile.)  Where it says 64 lanes the
 // cut tile is taken if it can be (measured in launch_obj).  A user objective up
 // to 8 dimensions gets 32 lanes: evaluated as a whole it tries one step length
 // per lane in a line-search round, and on four user sources (d = 2..5, 1.9 to 12 trials per iteration)

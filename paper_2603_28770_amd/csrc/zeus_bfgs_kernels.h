@@ -80,9 +80,9 @@ __device__ __forceinline__ V uniform(V v) {
 // flow splits only on values the whole group shares.
 // Waves per SIMD the register allocation must allow.  Left to itself the
 // compiler keeps the 64-lane kernels of the transcendental objectives at one
-// wave (256 VGPRs plus AGPRs); asking for two costs a few dozen spilled
-// registers but hides far more latency (Ackley d = 50: 1.5x faster), and
-// three waves help Rastrigin's 16-lane kernel the same way.  The polynomial
+// wave (256 VGPRs plus AGPRs); at two they take 242 to 255 VGPRs, nothing spilled,
+// and hide far more latency (Ackley d = 50: 1.5x faster), and three waves help
+// Rastrigin's 16-lane kernel the same way.  The polynomial
 // objectives' kernels lie a few registers above the next occupancy at 8 to 32
 // lanes (Rosenbrock d = 20 in mixed precision, 16,384 starts: 1.88 ms at two
 // waves, 1.57 at three; d = 10, 65,536 starts: 1.21 at three, 1.14 at four).  The

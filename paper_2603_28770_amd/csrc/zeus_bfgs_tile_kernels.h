@@ -19,8 +19,9 @@
 //    columns fit 168 registers and four blocks.  Rosenbrock, 8,192 starts:
 //    d = 96 35.0 -> 21.2 ms, d = 65 25.7 -> 15.4 ms (at two blocks still 32.5 and
 //    23.8); Styblinski-Tang d = 90 3.1 -> 1.9 ms; Ackley d = 70 1.77 -> 1.55 ms,
-//    with 67 registers spilled.  Columns split this way among four wavefronts
-//    need four pieces per row instead of two: d = 128 86.0 ms against 83.1;
+//    with 67 registers spilled (not in small launches, see tile_three).  Columns
+//    split this way among four wavefronts need four pieces per row instead of
+//    two: d = 128 86.0 ms against 83.1;
 //  * every wavefront keeps all coordinates (lane l the coordinates 2 l and
 //    2 l + 1) and forms value, gradient and sums for itself, so an iteration
 //    has three barriers: one after each product's pieces (u = H y and

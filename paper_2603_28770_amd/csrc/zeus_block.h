@@ -1,8 +1,11 @@
 // zeus_block.h -- pieces shared by the block-per-start BFGS kernels (64 < d):
 // one block of three, four or eight wavefronts runs a start.
-// Lane j owns coordinate j; the block exchanges vectors through its LDS
-// struct (a type with the members these helpers name: xs, ps, red, tsum,
-// pass, al and q) and finishes every sum across its wavefronts there.
+// The block exchanges vectors through its LDS struct (a type with the members
+// these helpers name: xs, ps, red, tsum, pass, al and q).  In the block of eight
+// wavefronts with H on chip (128 < d <= 208) lane j owns coordinate j and every sum
+// finishes across the wavefronts there (block_tree_sums, block_eval); in the
+// others every wavefront keeps all coordinates and needs no more than the search
+// (block_armijo).
 #pragma once
 
 #include "zeus_bfgs_common.h"
@@ -62,7 +65,7 @@ __device__ __forceinline__ double block_tree_sum(double v, Shm &sh, int &phase) 
 // over the same pairwise tree (the value's tree runs over every lane of the
 // block, the trial's over the first SLOTS slots, and the slots between hold
 // exact zeros) -- so they are taken as they are, and the sum and its
-// barrier are skipped (d = 128: 89.5 -> 87.3 ms, d = 200: 231.4 -> 225.4 ms).
+// barrier are skipped (d = 200: 231.4 -> 225.4 ms).
 // acc is uniform across the block.
 template <int OBJ, class T, bool kGrad, class Shm>
 __device__ __forceinline__ double block_eval(int d, const double *xs, double *gj, Shm &sh,

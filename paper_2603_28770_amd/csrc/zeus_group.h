@@ -753,8 +753,8 @@ __device__ __forceinline__ double slot_dot(const double (&a)[CPL], const double 
 // (wave_search): the same terms at the same point in the same number type
 // over the same pairwise tree of G * CPL slots, so they are the sums this
 // evaluation would form, and the value's butterflies are skipped (d = 200,
-// m = 8: 40.6 -> 39.5 ms).  In the BFGS lane-group kernel the same reuse saved
-// no time: there the value's butterfly overlaps other work.
+// m = 8: 40.6 -> 39.5 ms).  The BFGS kernels do the same where a start has a
+// wavefront or more (group_value_grad, block_eval).
 template <int OBJ, int G, int CPL, class T>
 __device__ __forceinline__ double value_grad_slots(const GroupLanes<G> &L, int d, const double *xs,
                                                    double (&gj)[CPL], const double *known = nullptr) {

@@ -13,8 +13,9 @@ namespace zeus {
 // Largest dimension of this build.  Up to kMaxNarrowDim a group of at most one
 // 64-lane wavefront runs a start with the inverse Hessian in its registers; up
 // to kTile3Dim a block of three wavefronts runs a start with H in their
-// registers, 32 columns each; up to kTileBlockDim a block of four runs a start
-// with H in the registers of its wavefronts, a 64 x 64 quarter each; up to
+// registers, 32 columns each (not in every launch, see tile_three); up to
+// kTileBlockDim a block of four runs a start with H in the registers of its
+// wavefronts, a 64 x 64 quarter each; up to
 // kHybridDim a block of eight wavefronts runs a start with eight 64 x 64 tiles
 // of H in its registers and the rest in LDS; above that a block of eight runs a
 // start with H in their registers, LDS and a slot in device memory.  As a

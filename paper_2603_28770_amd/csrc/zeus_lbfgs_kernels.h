@@ -19,7 +19,9 @@
 // coordinates took a butterfly of its own (four per sum at 256 slots), which
 // was most of the kernel.  Rosenbrock, m = 8: d = 200, 8,192 starts 40.1 ->
 // 21.3 ms (with one trial a round, below), d = 50, 65,536 starts 26.9 -> 11.9 ms,
-// d = 100, 8,192 starts 13.3 -> 6.3 ms.
+// d = 100, 8,192 starts 13.3 -> 6.3 ms.  Launches with few starts, and those that
+// end with a stalled one, wait for single iterations instead; they run with a
+// coordinate per lane (lbfgs_spread).
 #pragma once
 
 #include "zeus_bfgs_common.h"
@@ -47,9 +49,10 @@ __device__ __forceinline__ double value_slots(const GroupLanes<G> &L, int d, con
 }
 
 // Two waves per SIMD for the 4-coordinate kernels of the polynomial
-// objectives, which then fit 256 registers without spilling (the
-// transcendental ones would spill over a hundred and stay at one wave, and
-// user code is of unknown size).
+// objectives, which then take 245 to 256 registers: with 64 lanes up to 4 spilled,
+// with fewer 16 to 20 for Rosenbrock (18 to 30 in mixed precision) and 4 to 10 for
+// the others.  (The transcendental ones would spill over a hundred and stay at
+// one wave, and user code is of unknown size.)
 template <int OBJ, int CPL>
 constexpr int kLbfgsWaves =
     CPL == 4 && OBJ != kRastrigin && OBJ != kAckley && OBJ != kUser ? 2 : 1;
